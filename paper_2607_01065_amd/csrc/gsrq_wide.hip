@@ -129,7 +129,6 @@ struct WDeferPtrs {
   float* gmin;
   int* xcount;
   int* xchanged;
-  double* xobj;
   int* hcount;   // null: no single pass
 };
 
@@ -190,7 +189,6 @@ __global__ void __launch_bounds__(64) w_frag_kernel(const float* __restrict__ ga
     X.gmin[gridDim.y + cbl] = m;
     X.xcount[cbl] = 0;
     X.xchanged[cbl] = 0;
-    X.xobj[cbl] = 0.0;
     if (X.hcount) X.hcount[cbl] = 0;
   }
   u4* out = frag + ((size_t)cbl * tiles + t) * (2 * P + 1) * 64;
@@ -272,7 +270,6 @@ struct WScoreArgs {
   int* xcount;            // [G] rows deferred to the exact kernel (reset with sigma)
   int* xrows;             // [G][N] their row indices
   int* xchanged;          // [G] exact kernel: some deferred row changed code
-  double* xobj;           // [G] exact kernel: their weighted distortion
   int* hcount;            // [G] rows the single pass lists for the hi/lo pass
   int* hrows;             // [G][N] their row indices
   unsigned long long* hbest;  // [G][N] hi/lo pass: best (distance key, codeword) per listed row
@@ -283,11 +280,9 @@ struct WScoreArgs {
   const float* shape;     // [ncb][K][d]
   int unit_gain;          // score with unit gains (equal-gain initial assignment)
   // training outputs
-  const float* w;         // [N] or null (all ones)
   const int* done;        // [G] or null
   uint16_t* assign;       // [G][N]: old assignment in, new one out
   int* changed;           // [G][nwg]
-  double* obj;            // [G][nwg] or null
   // encode outputs
   uint32_t* codes;        // [N][words], zeroed beforehand, or null
   int words, b, m;
@@ -843,8 +838,8 @@ __device__ __forceinline__ void w_put_code(uint32_t* wp, int64_t bit, int b, int
 }
 
 // Scoring kernel: assignment (eq. 5) of every row of a chunk for one
-// subspace, then the mode's outputs (training: assignment, changed flag,
-// objective; encode: code bits and residual).  Grid: G x nwg workgroups,
+// subspace, then the mode's outputs (training: assignment and changed flag;
+// encode: code bits and residual).  Grid: G x nwg workgroups,
 // numbered so that subspaces whose rows share cache lines run on one XCD.
 // Waves per SIMD: four (two workgroups per CU) with a resident table and
 // narrow rows; two when d >= 64 (row operands up to 68 VGPRs) or when the
@@ -868,7 +863,6 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
   constexpr int NTH = NW * 64;
   constexpr int WR = NW * RB;   // rows of a round per row block of the waves
   extern __shared__ __align__(16) u4 wtab[];
-  __shared__ double red_obj[NW];
   __shared__ int red_changed;
   constexpr bool F16 = sizeof(T) == 2;
   constexpr int P = w_pairs(C);
@@ -919,8 +913,8 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
   const T* X = (const T*)a.x;
   const bool vec = (d == 8 * C) && ((a.ldx * (int64_t)sizeof(T)) % 16 == 0) &&
                    (((uintptr_t)X) % 16 == 0);
-  // vector accesses in the residual / objective epilogue: row, codeword and
-  // residual output aligned (d is a multiple of 8)
+  // vector accesses in the residual epilogue: row, codeword and residual
+  // output aligned (d is a multiple of 8)
   const bool rvec = vec && (((uintptr_t)scb) % 16 == 0) &&
                     (a.res_out == nullptr || ((uintptr_t)a.res_out) % 16 == 0);
   if (tid == 0) red_changed = 0;
@@ -933,7 +927,6 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
   }
   __syncthreads();
 
-  double obj = 0.0;
   bool any_changed = false;
   // this lane's row of round rd, row block r of the wave (valid: below N,
   // or within the list)
@@ -1133,27 +1126,19 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
       if (kstar >= K) kstar = K - 1;   // deferred rows and rows past N only
       const bool own = valid[r] && !defer && !relist;
 
-      const float gk = a.unit_gain ? 1.f : gcb[kstar];
-      const float* sk = scb + (size_t)kstar * d;
       if (MODE == W_TRAIN) {
         if (own && h == 0) {
           uint16_t* ap = a.assign + (size_t)g * a.N + row[r];
           if (*ap != (uint16_t)kstar) any_changed = true;
           *ap = (uint16_t)kstar;
         }
-        if (a.obj) {
-          // weighted distortion of this assignment under the scoring codebook;
-          // each lane half sums half of the elements
-          const int jb = h * (d / 2);
-          float dist = w_residual<T, (P <= 8)>(xp[r] + jb, sk + jb, gk, d / 2, rvec, nullptr);
-          dist += __shfl_xor(dist, 32);
-          if (own && h == 0) obj += (double)(a.w ? a.w[row[r]] : 1.f) * (double)dist;
-        }
       } else {
         if (own && h == 0 && a.codes)
           w_put_code(a.codes + row[r] * a.words, ((int64_t)a.m * a.G + g) * a.b, a.b, kstar);
         if (own && a.res_out) {
           // each lane half writes its half of the row's residual
+          const float gk = a.unit_gain ? 1.f : gcb[kstar];
+          const float* sk = scb + (size_t)kstar * d;
           const int jb = h * (d / 2);
           float* dst = a.res_out + row[r] * ((int64_t)a.G * d) + (int64_t)g * d + jb;
           w_residual<T, (P <= 8)>(xp[r] + jb, sk + jb, gk, d / 2, rvec, dst);
@@ -1164,17 +1149,9 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
     if constexpr (R == 2) finish_block(1);
   }
   if (MODE == W_TRAIN && !IND) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) obj += __shfl_xor(obj, off);
-    if (lane == 0) red_obj[wave] = obj;
     if (__ballot(any_changed) && lane == 0) atomicOr(&red_changed, 1);
     __syncthreads();
-    if (tid == 0) {
-      double s = 0.0;
-      for (int w = 0; w < NW; ++w) s += red_obj[w];
-      a.changed[(size_t)g * a.nwg + rc] = red_changed;
-      if (a.obj) a.obj[(size_t)g * a.nwg + rc] = s;
-    }
+    if (tid == 0) a.changed[(size_t)g * a.nwg + rc] = red_changed;
   }
 }
 
@@ -1583,28 +1560,23 @@ __global__ void __launch_bounds__(W_FW_THREADS, 1) w_encode_fused_wide_kernel(WF
 // each row's best (distance key, codeword) from hbest is checked like a row
 // of the scoring kernel (operands in the float16 range, best distance at
 // most twice the row's energy) and either appended to the exact kernel's
-// list or written out: training the assignment, the stop flag (xchanged)
-// and the weighted distortion (xobj); encode the code bits and the
-// residual.  Lane groups of W_LF_LANES lanes take one listed row each,
-// grid-stride over the list.
+// list or written out: training the assignment and the stop flag
+// (xchanged); encode the code bits and the residual.  Training takes one
+// row per lane, encode one per group of W_LF_LANES lanes, grid-stride over
+// the list.
 // What bounds it: the chain of dependent loads of a row (row id and key,
-// then the row and its codeword), so 16 rows per workgroup round are in
-// flight.  The objective leaves a workgroup as one atomic: one float64
-// atomic per row on the few addresses of xobj serialised the whole GPU
-// (65536 x 1024 float32 rows, K = 4096, about a quarter of the rows listed:
-// 489 us with an atomic per row, one wave per row; the case 4523 -> 3231 us).
+// then the old assignment, or the row and its codeword).
 constexpr int W_LF_LANES = 16;
 constexpr int W_LF_WGS = 128;    // workgroups per subspace
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256) w_listed_finish_kernel(WScoreArgs a) {
-  __shared__ double wobj[4];
   const int g = blockIdx.y;
   if (a.done && a.done[g]) return;
   const int cnt = a.hcount[g];
-  constexpr int RPB = 256 / W_LF_LANES;             // rows per workgroup round
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int q = lane & (W_LF_LANES - 1);
+  constexpr int LPR = MODE == W_TRAIN ? 1 : W_LF_LANES;   // lanes per row
+  constexpr int RPB = 256 / LPR;                          // rows per workgroup round
+  const int q = threadIdx.x % LPR;
   const int d = a.d, K = a.K;
   const int cb = a.cb0 + g;
   const float* gcb = a.gain + (size_t)cb * K;
@@ -1615,9 +1587,7 @@ __global__ void __launch_bounds__(256) w_listed_finish_kernel(WScoreArgs a) {
   const bool vec = (((uintptr_t)X) % 16 == 0) && ((a.ldx * (int64_t)sizeof(T)) % 16 == 0) &&
                    (((uintptr_t)scb) % 16 == 0) &&
                    (a.res_out == nullptr || ((uintptr_t)a.res_out) % 16 == 0);
-  double obj = 0.0;
-  for (int idx = blockIdx.x * RPB + (int)(threadIdx.x / W_LF_LANES); idx < cnt;
-       idx += gridDim.x * RPB) {
+  for (int idx = blockIdx.x * RPB + (int)threadIdx.x / LPR; idx < cnt; idx += gridDim.x * RPB) {
     const size_t li = (size_t)g * a.N + idx;
     const int64_t row = a.hrows[li];
     const unsigned long long key = a.hbest[li];
@@ -1631,43 +1601,25 @@ __global__ void __launch_bounds__(256) w_listed_finish_kernel(WScoreArgs a) {
       }
       continue;
     }
-    const float gk = a.unit_gain ? 1.f : gcb[kstar];
-    const float* sk = scb + (size_t)kstar * d;
-    const T* xp = X + row * a.ldx + (int64_t)g * d;
-    float* dst = nullptr;
-    if (MODE == W_ENCODE && a.res_out) dst = a.res_out + row * ((int64_t)a.G * d) + (int64_t)g * d;
-    if (MODE == W_TRAIN ? a.obj != nullptr : dst != nullptr) {
-      float dist = 0.f;
-      if (vec) {
-        for (int j = 4 * q; j < d; j += 4 * W_LF_LANES)
-          dist += w_residual<T>(xp + j, sk + j, gk, 4, true, dst ? dst + j : nullptr);
-      } else {
-        for (int j = q; j < d; j += W_LF_LANES)
-          dist += w_residual<T>(xp + j, sk + j, gk, 1, false, dst ? dst + j : nullptr);
-      }
-      if (MODE == W_TRAIN) {
-#pragma unroll
-        for (int off = W_LF_LANES / 2; off > 0; off >>= 1) dist += __shfl_xor(dist, off);
-        if (q == 0) obj = fma((double)(a.w ? a.w[row] : 1.f), (double)dist, obj);
-      }
-    }
-    if (q == 0) {
-      if (MODE == W_TRAIN) {
-        uint16_t* ap = a.assign + (size_t)g * a.N + row;
-        if (*ap != (uint16_t)kstar) a.xchanged[g] = 1;
-        *ap = (uint16_t)kstar;
-      } else if (a.codes) {
+    if (MODE == W_TRAIN) {
+      uint16_t* ap = a.assign + (size_t)g * a.N + row;
+      if (*ap != (uint16_t)kstar) a.xchanged[g] = 1;
+      *ap = (uint16_t)kstar;
+    } else {
+      if (q == 0 && a.codes)
         w_put_code(a.codes + row * a.words, ((int64_t)a.m * a.G + g) * a.b, a.b, kstar);
+      if (a.res_out) {
+        const float gk = gcb[kstar];
+        const float* sk = scb + (size_t)kstar * d;
+        const T* xp = X + row * a.ldx + (int64_t)g * d;
+        float* dst = a.res_out + row * ((int64_t)a.G * d) + (int64_t)g * d;
+        if (vec) {
+          for (int j = 4 * q; j < d; j += 4 * LPR) w_residual<T>(xp + j, sk + j, gk, 4, true, dst + j);
+        } else {
+          for (int j = q; j < d; j += LPR) w_residual<T>(xp + j, sk + j, gk, 1, false, dst + j);
+        }
       }
     }
-  }
-  if (MODE == W_TRAIN && a.obj) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) obj += __shfl_xor(obj, off);
-    if (lane == 0) wobj[wave] = obj;
-    __syncthreads();
-    if (threadIdx.x == 0 && (int)blockIdx.x * RPB < cnt)
-      atomicAdd(a.xobj + g, wobj[0] + wobj[1] + wobj[2] + wobj[3]);
   }
 }
 
@@ -1693,10 +1645,9 @@ constexpr int W_XKMAX = 4096;    // candidate list capacity (codewords)
 template <typename T, int MODE>
 __global__ void __launch_bounds__(W_XTHREADS) w_exact_kernel(WScoreArgs a) {
   __shared__ __align__(16) double xsd[W_XROWS][8 * W_CMAX];
-  __shared__ double xn[W_XROWS], xq[W_XROWS];
+  __shared__ double xn[W_XROWS];
   __shared__ double wbd[W_XTHREADS / 64][W_XROWS];
   __shared__ int wbk[W_XTHREADS / 64][W_XROWS];
-  __shared__ double bestd[W_XROWS];
   __shared__ int bestk[W_XROWS];
   __shared__ int rows[W_XROWS];
   __shared__ int olda[W_XROWS];
@@ -1768,7 +1719,6 @@ __global__ void __launch_bounds__(W_XTHREADS) w_exact_kernel(WScoreArgs a) {
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off);
       if (lane == 0) {
-        xq[wave * 4 + r] = q;
         xn[wave * 4 + r] = sqrt(q);
       }
     }
@@ -1901,7 +1851,6 @@ __global__ void __launch_bounds__(W_XTHREADS) w_exact_kernel(WScoreArgs a) {
         if (od < b || (od == b && ok < k)) { b = od; k = ok; }
       }
       bestk[tid] = k < K ? k : 0;           // (a non-empty list always sets k)
-      bestd[tid] = b;
     }
     __syncthreads();
     // outputs: wave w writes rows w, w + 4, w + 8, w + 12
@@ -1913,10 +1862,6 @@ __global__ void __launch_bounds__(W_XTHREADS) w_exact_kernel(WScoreArgs a) {
       const int k = bestk[i];
       if (MODE == W_TRAIN) {
         if (lane == 0) {
-          // weighted distortion ||x - g s||^2 = ||x||^2 + (g^2 - 2 g s.x)
-          // of the chosen codeword, both terms in float64
-          if (a.obj)
-            atomicAdd(a.xobj + g, (double)(a.w ? a.w[row] : 1.f) * (xq[i] + bestd[i]));
           if (olda[i] != k) a.xchanged[g] = 1;
           a.assign[(size_t)g * a.N + row] = (uint16_t)k;
         }
@@ -2069,12 +2014,36 @@ __global__ void __launch_bounds__(256) w_bucket_scatter_kernel(const uint16_t* _
     srt[atomicAdd(&cur[asg[r]], 1)] = (int)r;
 }
 
+// Value of another lane by a DPP move (the VALU's own lane crossing).
+template <int CTRL> __device__ __forceinline__ float w_dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL> __device__ __forceinline__ double w_dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Sum over aligned groups of L lanes (a power of two up to 64, uniform), in
+// every lane.  Up to 16 lanes it stays off the LDS pipe that shuffles share
+// with the float64 atomics of w_acc_members.
+template <typename V> __device__ __forceinline__ V w_group_sum(V v, int L) {
+  if (L >= 2) v += w_dpp<0xB1>(v);      // quad_perm [1, 0, 3, 2]
+  if (L >= 4) v += w_dpp<0x4E>(v);      // quad_perm [2, 3, 0, 1]
+  if (L >= 8) v += w_dpp<0x141>(v);     // mirror within 8 lanes: the other quad
+  if (L >= 16) v += w_dpp<0x140>(v);    // mirror within 16 lanes: the other half
+  if (L >= 32) v += __shfl_xor(v, 16);
+  if (L >= 64) v += __shfl_xor(v, 32);
+  return v;
+}
+
 // Batched member loop of the accumulation: members [0, n), member `it` is
-// row row_of(it) of codeword asg[row] in [k0, k0 + ks).  Lane groups of d / E
-// lanes take one member each (E elements per lane), W_ACC_MEMBERS members
-// per lane group in flight: every load of a batch is issued before the
-// first use (past the end a lane group re-reads its first member and adds
-// nothing).
+// row row_of(it) of codeword asg[row] in [k0, k0 + ks).  Lane groups of L =
+// d / E lanes take one member each (lane i of a group the E elements
+// i + L e, so that a group's atomics fall on consecutive float64 words),
+// W_ACC_MEMBERS members per lane group in flight: every load of a batch is
+// issued before the first use (past the end a lane group re-reads its first
+// member and adds nothing).
 template <typename T, int E, typename RowOf>
 __device__ __forceinline__ void w_acc_members(const WAccArgs& a, int g, int k0, double* wacc,
                                               int n, RowOf row_of) {
@@ -2096,7 +2065,7 @@ __device__ __forceinline__ void w_acc_members(const WAccArgs& a, int g, int k0, 
       k[u] = asg[row];
       const T* xr = X + row * a.ldx + (int64_t)g * d;
 #pragma unroll
-      for (int e = 0; e < E; ++e) xv[u][e] = (float)xr[E * li + e];
+      for (int e = 0; e < E; ++e) xv[u][e] = (float)xr[li + L * e];
       wt[u] = a.w ? a.w[row] : 1.f;
     }
 #pragma unroll
@@ -2104,26 +2073,34 @@ __device__ __forceinline__ void w_acc_members(const WAccArgs& a, int g, int k0, 
       float ss = xv[u][E - 1] * xv[u][E - 1];
 #pragma unroll
       for (int e = E - 2; e >= 0; --e) ss = fmaf(xv[u][e], xv[u][e], ss);
-      for (int off = L / 2; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+      ss = w_group_sum(ss, L);
       if (it0 + u * stride >= n) continue;   // uniform within the lane group
       const float inv = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ss) + Y_EPS);
       double* ak = wacc + (size_t)(k[u] - k0) * S;
 #pragma unroll
       for (int e = 0; e < E; ++e)
-        unsafeAtomicAdd(ak + E * li + e, (double)(xv[u][e] * (wt[u] * inv)));
+        unsafeAtomicAdd(ak + li + L * e, (double)(xv[u][e] * (wt[u] * inv)));
+      double q = 0.0;
 #pragma unroll
-      for (int e = 0; e < E; ++e) unsafeAtomicAdd(ak + d + E * li + e, (double)(xv[u][e] * wt[u]));
+      for (int e = 0; e < E; ++e) {
+        const double x = xv[u][e], p = x * (double)wt[u];
+        unsafeAtomicAdd(ak + d + li + L * e, p);
+        q = fma(p, x, q);
+      }
+      q = w_group_sum(q, L);
       if (li == 0) {
         unsafeAtomicAdd(ak + 2 * d, (double)wt[u]);
-        unsafeAtomicAdd(ak + 2 * d + 1, 1.0);
+        unsafeAtomicAdd(ak + 2 * d + 1, q);
       }
     }
   }
 }
 
 // Weighted sums of eqs. 6-8 for one (codeword slice, row chunk, subspace):
-// sum w y and sum w x (y = x / (||x|| + eps)), sum w and the member count
-// per codeword, accumulated in float64 LDS and written as one partial.
+// sum w y and sum w x (y = x / (||x|| + eps)), sum w and sum w ||x||^2 per
+// codeword, accumulated in float64 LDS and written as one partial.  The
+// last two and sum w x are exact to float64 rounding (float64 products of
+// float32 factors): the objective is a difference of them.
 // Members: with one slice, every row of the chunk; with bucketed rows, the
 // chunk's share of the slice's buckets; otherwise the chunk's members of
 // the slice, collected into an LDS list first.  E elements per lane: 2, or
@@ -2234,14 +2211,14 @@ __global__ void __launch_bounds__(256) w_accumulate_sorted_kernel(WAccArgs a) {
   const int* bo = a.boff + (size_t)g * (a.K + 1);
   const int nkb = (a.K + 3) / 4;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int m0, m1, mall;
+  int m0, m1;
   double* out;
   if ((int)blockIdx.x < nkb) {
     const int k = blockIdx.x * 4 + wv;
     if (k >= a.K) return;   // uniform per wave
     m0 = bo[k];
-    mall = bo[k + 1];
-    m1 = a.ovf ? min(mall, m0 + W_SORT_Q) : mall;
+    m1 = bo[k + 1];
+    if (a.ovf) m1 = min(m1, m0 + W_SORT_Q);
     out = a.part + ((size_t)g * a.rchunks * a.K + k) * S;
   } else {
     const int i = ((int)blockIdx.x - nkb) * 4 + wv;
@@ -2250,12 +2227,11 @@ __global__ void __launch_bounds__(256) w_accumulate_sorted_kernel(WAccArgs a) {
     if (k < 0) return;
     m0 = max(i * W_SORT_Q, bo[k] + W_SORT_Q);
     m1 = min(i * W_SORT_Q + W_SORT_Q, bo[k + 1]);
-    mall = m1;
     out = a.ovf + ((size_t)g * a.nwin + i) * S;
   }
   const int* srt = a.sorted + (size_t)g * a.N;
   const T* X = (const T*)a.x + (int64_t)g * d + E * li;
-  double sy[E], sx[E], wsum = 0.0;
+  double sy[E], sx[E], wsum = 0.0, qsum = 0.0;   // qsum: sum w ||x||^2 of the lane's elements
 #pragma unroll
   for (int e = 0; e < E; ++e) sy[e] = sx[e] = 0.0;
   constexpr int STEP = 4 * SM;   // members per batch and wave
@@ -2292,7 +2268,9 @@ __global__ void __launch_bounds__(256) w_accumulate_sorted_kernel(WAccArgs a) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           sy[e] += (double)(xv[u][e] * (wt[u] * inv));
-          sx[e] += (double)(xv[u][e] * wt[u]);
+          const double x = xv[u][e], p = x * (double)wt[u];
+          sx[e] += p;
+          qsum = fma(p, x, qsum);
         }
         wsum += (double)wt[u];
       }
@@ -2308,6 +2286,8 @@ __global__ void __launch_bounds__(256) w_accumulate_sorted_kernel(WAccArgs a) {
     }
     wsum += __shfl_xor(wsum, off);
   }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) qsum += __shfl_xor(qsum, off);
   if (grp == 0) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -2316,7 +2296,7 @@ __global__ void __launch_bounds__(256) w_accumulate_sorted_kernel(WAccArgs a) {
     }
     if (li == 0) {
       out[2 * d] = wsum;
-      out[2 * d + 1] = (double)(mall - m0);
+      out[2 * d + 1] = qsum;
     }
   }
 }
@@ -2327,7 +2307,7 @@ struct WFinArgs {
   int no_early_stop, force_changed, nwg;
   const double* part;     // [G][rchunks][K][2d+2]
   const int* changed;     // [G][nwg]
-  const double* obj;      // [G][nwg] or null
+  double* obj;            // [2][G][blocks per subspace], by iteration parity; null: no trace
   const float* seednorm;  // [G][K]
   float* gain;            // [G][K]
   float* shape;           // [G][K][d]
@@ -2335,7 +2315,6 @@ struct WFinArgs {
   int* iters;             // [G]
   double* trace;          // [G][T] or null
   const int* xchanged;    // [G] changed flag of the exact kernel's rows
-  const double* xobj;     // [G] their objective
   int kmeans;             // K-means baseline update instead of eqs. (7)(8)
   const double* ovf;      // [G][nwin][2d+2] window partials of the sorted sums, or null
   const int* boff;        // [G][K + 1] bucket offsets (with ovf)
@@ -2346,17 +2325,58 @@ struct WFinArgs {
 // codeword, E elements per lane (E = 2, or 4 for d = 256).  Initial pass (t = 0): eq. (8) gains for
 // the seed shapes (a codeword without members keeps its seed row's norm).
 // Iteration: eqs. (7) and (8) with the safeguards; thread 0 of block 0
-// applies the stop test of its subspace.  The trace entry (zeroed by the
-// host) receives the objective by atomic adds.  K-means baseline: centroid
-// = (sum w x) / W, held as norm and direction, and the trace is the
-// distortion after the update, J_before - sum_k W_k ||m_k - c_k||^2 (the
-// weighted mean m_k replacing the old centroid c_k), each block adding its
-// codewords' share.
+// applies the stop test of its subspace.
+// Objective, from the same sums (no pass over the rows computes it: the
+// scoring launch that read every row and its codeword again for it took
+// @OBJ): of the assignment just made against the codebook it was made with,
+//   sum_i w_i ||x_i - g s||^2 = sum_k [sum w ||x||^2 - g_k (2 s_k . S_k - g_k ||s_k||^2 W_k)],
+// S_k = sum w x and W_k = sum w of codeword k's members, everything in
+// float64 from exact products, so the cancellation costs no accuracy.
+// K-means baseline: centroid = S_k / W_k, held as norm and direction, and
+// the trace is the distortion after the update,
+// sum_k [sum w ||x||^2 - ||S_k||^2 / W_k].  Every block leaves its codewords'
+// share in obj; the next launch's block 0 (w_trace_kernel after the last
+// iteration) adds them in block order, so the trace does not depend on the
+// order in which blocks run.
+
+// Trace entry of iteration t of subspace g from the blocks' shares (a wave).
+__device__ __forceinline__ void w_trace_entry(const double* obj, double* trace, int g, int G,
+                                              int nblk, int T, int t) {
+  const double* o = obj + ((size_t)(t & 1) * G + g) * nblk;
+  const int lane = threadIdx.x & 63;
+  double v = 0.0;
+  constexpr int UN = 8;                // loads in flight per lane
+  for (int c0 = lane; c0 < nblk; c0 += UN * 64) {
+    double x[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) x[u] = o[min(c0 + 64 * u, nblk - 1)];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) v += c0 + 64 * u < nblk ? x[u] : 0.0;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  if (lane == 0) trace[(size_t)g * T + (t - 1)] = v;
+}
+
+// The last iteration's trace entries (earlier ones: w_finalize_kernel).
+__global__ void __launch_bounds__(64) w_trace_kernel(const double* obj, double* trace,
+                                                     const int* done, int G, int nblk, int T) {
+  const int g = blockIdx.x;
+  if (done[g] != 0 && done[g] < T) return;
+  w_trace_entry(obj, trace, g, G, nblk, T, T);
+}
+
 template <int E>
 __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
   __shared__ double red[4];
   const int g = blockIdx.y;
-  if (a.t > 0 && a.done[g] != 0 && a.done[g] < a.t) return;
+  const int stopped = a.t > 0 ? a.done[g] : 0;
+  // the previous iteration's trace entry (also when the subspace stopped
+  // in it), by the last wave of block 0
+  if (a.t > 1 && a.trace && blockIdx.x == 0 && threadIdx.x >= 192 &&
+      (stopped == 0 || stopped >= a.t - 1))
+    w_trace_entry(a.obj, a.trace, g, a.G, gridDim.x, a.T, a.t - 1);
+  if (stopped != 0 && stopped < a.t) return;
   const int d = a.d, K = a.K, S = 2 * d + 2;
   const int L = d / E;                 // lanes per codeword (power of two, <= 64)
   const int tid = threadIdx.x;
@@ -2364,7 +2384,7 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
   const int li = tid % L;
   const bool active = k < K;
   const int kk = active ? k : K - 1;
-  double sy[E], sx[E], W = 0;
+  double sy[E], sx[E], W = 0, Q = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) sy[e] = sx[e] = 0.0;
   for (int c = 0; c < a.rchunks; ++c) {
@@ -2375,6 +2395,7 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
       sx[e] += p[d + E * li + e];
     }
     W += p[2 * d];
+    Q += p[2 * d + 1];
   }
   if (a.ovf) {
     // the codeword's members past its first W_SORT_Q, window by window
@@ -2389,6 +2410,7 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
           sx[e] += p[d + E * li + e];
         }
         W += p[2 * d];
+        Q += p[2 * d + 1];
       }
   }
   float* sk = a.shape + ((size_t)g * K + kk) * d;
@@ -2397,38 +2419,32 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
 #pragma unroll
   for (int e = 0; e < E; ++e) sv[e] = sk[E * li + e];
   double gnew = (a.t == 0) ? (double)a.seednorm[(size_t)g * K + kk] : (double)*gk;
+  // this lane's share of the codeword's objective term
+  double term = active && li == 0 ? Q : 0.0;
   if (a.t > 0 && a.kmeans) {
-    double drop = 0.0;
     if (W > 0.0) {
-      double c[E], ee[E];
+      double c[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        c[e] = sx[e] / W;
-        ee[e] = c[e] - gnew * sv[e];
-      }
-      double q = ee[E - 1] * ee[E - 1], cn = c[E - 1] * c[E - 1];
+      for (int e = 0; e < E; ++e) c[e] = sx[e] / W;
+      double cn = c[E - 1] * c[E - 1];
 #pragma unroll
-      for (int e = E - 2; e >= 0; --e) {
-        q = fma(ee[e], ee[e], q);
-        cn = fma(c[e], c[e], cn);
-      }
-      drop = W * q;
+      for (int e = E - 2; e >= 0; --e) cn = fma(c[e], c[e], cn);
+      if (active) term -= W * cn;
       for (int off = L / 2; off > 0; off >>= 1) cn += __shfl_xor(cn, off);
       cn = sqrt(cn);
 #pragma unroll
       for (int e = 0; e < E; ++e) sv[e] = cn > 0.0 ? c[e] / cn : 0.0;
       gnew = cn;
     }
-    if (!active) drop = 0.0;
-    if (a.trace) {
-      for (int off = 32; off > 0; off >>= 1) drop += __shfl_xor(drop, off);
-      if ((tid & 63) == 0) red[tid >> 6] = drop;
-      __syncthreads();
-      if (tid == 0)
-        atomicAdd(a.trace + (size_t)g * a.T + (a.t - 1), -(red[0] + red[1] + red[2] + red[3]));
-    }
   } else if (W > 0.0) {
     if (a.t > 0) {
+      double ps = 0.0, s2 = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        ps = fma(sx[e], sv[e], ps);
+        s2 = fma(sv[e], sv[e], s2);
+      }
+      if (active) term -= gnew * (2.0 * ps - gnew * s2 * W);
       double mn = sy[E - 1] * sy[E - 1];
 #pragma unroll
       for (int e = E - 2; e >= 0; --e) mn = fma(sy[e], sy[e], mn);
@@ -2450,22 +2466,21 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
     for (int e = 0; e < E; ++e) sk[E * li + e] = (float)sv[e];
     if (li == 0) *gk = (float)gnew;
   }
+  if (a.t > 0 && a.trace) {
+    for (int off = 32; off > 0; off >>= 1) term += __shfl_xor(term, off);
+    if ((tid & 63) == 0) red[tid >> 6] = term;
+    __syncthreads();
+    if (tid == 0)
+      a.obj[((size_t)(a.t & 1) * a.G + g) * gridDim.x + blockIdx.x] =
+          red[0] + red[1] + red[2] + red[3];
+  }
   if (a.t > 0 && blockIdx.x == 0 && tid < 64) {
-    // stop test: the scoring workgroups' changed flags and objectives,
-    // strided over the first wave and reduced in a fixed order
+    // stop test: the scoring workgroups' changed flags
     int ch = 0;
-    double obj = 0.0;
-    for (int c = tid; c < a.nwg; c += 64) {
-      ch |= a.changed[(size_t)g * a.nwg + c];
-      if (a.obj) obj += a.obj[(size_t)g * a.nwg + c];
-    }
+    for (int c = tid; c < a.nwg; c += 64) ch |= a.changed[(size_t)g * a.nwg + c];
     const bool any = __ballot(ch != 0) != 0ull;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) obj += __shfl_xor(obj, off);
     if (tid == 0) {
       const bool changed = any || a.force_changed || a.xchanged[g];
-      if (a.obj) obj += a.xobj[g];
-      if (a.trace) atomicAdd(a.trace + (size_t)g * a.T + (a.t - 1), obj);
       a.iters[g] = a.t;
       if (!changed && !a.no_early_stop) a.done[g] = a.t;
     }
@@ -2886,14 +2901,12 @@ gsrq_status w_score_launch(const WScoreArgs& a, const WLayout& L, hipStream_t st
 }
 
 // Deferred-row state of the G codebooks a scoring launch uses: smallest
-// gains, row lists and what the exact kernel adds to the stop test and the
-// objective.
+// gains, row lists and what the exact kernel adds to the stop test.
 struct WDefer {
   float* gmin;      // [G] smallest gains, then [G] largest
   int* xcount;      // [G]
   int* xrows;       // [G][N]
   int* xchanged;    // [G]
-  double* xobj;     // [G]
   int* hcount;      // [G] rows listed by the single pass (null: no single pass)
   int* hrows;       // [G][N]
   unsigned long long* hbest;   // [G][N]
@@ -2909,7 +2922,7 @@ gsrq_status w_build_frags(const float* gain, const float* shape, int d, int K, i
   const int tiles = (K + CW - 1) / CW;
   const dim3 fgrid(tiles, ncb);
   const int ug = unit_gain ? 1 : 0;
-  const WDeferPtrs xp{X.gmin, X.xcount, X.xchanged, X.xobj, X.hcount};
+  const WDeferPtrs xp{X.gmin, X.xcount, X.xchanged, X.hcount};
   auto go = [&](auto kern) {
     kern<<<fgrid, 64, 0, st>>>(gain, shape, d, K, ug, sig, done, G, cb0, frag, xp);
   };
@@ -2978,8 +2991,15 @@ WAccLayout w_acc_layout(const gsrq_shape* s) {
   return A;
 }
 
+// Workgroups per subspace of the update kernel: lane groups of d / E lanes
+// per codeword, E = 2 elements per lane (4 at d = 256: at most one wave).
+int w_fin_blocks(const gsrq_shape* s) {
+  const int cpb = 256 / (s->d / (s->d > 128 ? 4 : 2));
+  return (s->K + cpb - 1) / cpb;
+}
+
 struct WTrainWs {
-  size_t frag, gmin, xcount, xrows, xchanged, xobj, hcount, hrows, hbest, hrr, sig, part,
+  size_t frag, gmin, xcount, xrows, xchanged, hcount, hrows, hbest, hrr, sig, part,
       changed, obj, assign, done, iters, seednorm, seeds, sorted, boff, bcnt, ovf, wk, total;
 };
 
@@ -2995,7 +3015,6 @@ WTrainWs w_train_ws(const gsrq_shape* s, size_t x_elt) {
   W.xcount = off; off = align256(off + (size_t)G * sizeof(int));
   W.xrows = off; off = align256(off + (size_t)G * s->N * sizeof(int));
   W.xchanged = off; off = align256(off + (size_t)G * sizeof(int));
-  W.xobj = off; off = align256(off + (size_t)G * sizeof(double));
   W.hcount = off; off = align256(off + (L16.sp ? (size_t)G * sizeof(int) : 0));
   W.hrows = off; off = align256(off + (L16.sp ? (size_t)G * s->N * sizeof(int) : 0));
   W.hbest = off; off = align256(off + (L16.sp ? (size_t)G * s->N * 8 : 0));
@@ -3004,7 +3023,7 @@ WTrainWs w_train_ws(const gsrq_shape* s, size_t x_elt) {
   W.part = off;
   off = align256(off + (size_t)G * A.rchunks * s->K * (2 * s->d + 2) * sizeof(double));
   W.changed = off; off = align256(off + (size_t)G * L16.nwg * sizeof(int));
-  W.obj = off; off = align256(off + (size_t)G * L16.nwg * sizeof(double));
+  W.obj = off; off = align256(off + 2 * (size_t)G * w_fin_blocks(s) * sizeof(double));
   W.assign = off; off = align256(off + (size_t)G * s->N * sizeof(uint16_t));
   W.done = off; off = align256(off + (size_t)G * sizeof(int));
   W.iters = off; off = align256(off + (size_t)G * sizeof(int));
@@ -3023,7 +3042,7 @@ WTrainWs w_train_ws(const gsrq_shape* s, size_t x_elt) {
 }
 
 struct WEncWs {
-  size_t frag, gmin, xcount, xrows, xchanged, xobj, hcount, hrows, hbest, hrr, sig, res0, res1,
+  size_t frag, gmin, xcount, xrows, xchanged, hcount, hrows, hbest, hrr, sig, res0, res1,
       total;
 };
 
@@ -3057,7 +3076,6 @@ WEncWs w_encode_ws(const gsrq_shape* s) {
     W.xcount = off; off = align256(off + ncb * sizeof(int));
     W.xrows = off;
     W.xchanged = off; off = align256(off + ncb * sizeof(int));
-    W.xobj = off; off = align256(off + ncb * sizeof(double));
     W.hcount = W.hrows = W.hbest = W.hrr = off;
     W.sig = off; off = align256(off + ncb * sizeof(int));
     W.res0 = W.res1 = off;
@@ -3069,7 +3087,6 @@ WEncWs w_encode_ws(const gsrq_shape* s) {
   W.xcount = off; off = align256(off + (size_t)G * sizeof(int));
   W.xrows = off; off = align256(off + (size_t)G * s->N * sizeof(int));
   W.xchanged = off; off = align256(off + (size_t)G * sizeof(int));
-  W.xobj = off; off = align256(off + (size_t)G * sizeof(double));
   W.hcount = off; off = align256(off + (L.sp ? (size_t)G * sizeof(int) : 0));
   W.hrows = off; off = align256(off + (L.sp ? (size_t)G * s->N * sizeof(int) : 0));
   W.hbest = off; off = align256(off + (L.sp ? (size_t)G * s->N * 8 : 0));
@@ -3098,7 +3115,7 @@ gsrq_status w_encode_stage(const gsrq_shape* s, int m, const void* x, int64_t ld
   a.tiles = L.tiles; a.QF = L.QF; a.cb0 = m * a.G; a.fcb0 = m * a.G;
   a.frag = frag; a.sig = sig; a.gain = gain; a.shape = shape; a.unit_gain = 0;
   a.gmin = X.gmin; a.xcount = X.xcount; a.xrows = X.xrows; a.xchanged = X.xchanged;
-  a.xobj = X.xobj; a.hcount = X.hcount; a.hrows = X.hrows; a.hbest = X.hbest; a.hrr = X.hrr;
+  a.hcount = X.hcount; a.hrows = X.hrows; a.hbest = X.hbest; a.hrr = X.hrr;
   a.codes = codes; a.words = words; a.b = log2i(s->K); a.m = m; a.res_out = res_out;
   a.nwg = L.nwg; a.rounds = L.rounds; a.tpc = L.tpc; a.map_xcd = L.map_xcd; a.lg = L.lg;
   return w_score_and_exact<T, W_ENCODE>(a, L, GSRQ_KERNEL_ENCODE, st);
@@ -3118,7 +3135,7 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   char* base = (char*)ws;
   u4* frag = (u4*)(base + W.frag);
   const WDefer XD = {(float*)(base + W.gmin), (int*)(base + W.xcount), (int*)(base + W.xrows),
-                     (int*)(base + W.xchanged), (double*)(base + W.xobj),
+                     (int*)(base + W.xchanged),
                      W.hrows > W.hcount ? (int*)(base + W.hcount) : nullptr,
                      W.hrows > W.hcount ? (int*)(base + W.hrows) : nullptr,
                      W.hrows > W.hcount ? (unsigned long long*)(base + W.hbest) : nullptr,
@@ -3142,10 +3159,10 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   sa.x = X; sa.ldx = ldx; sa.N = s->N; sa.d = d; sa.K = K; sa.G = G;
   sa.tiles = L.tiles; sa.QF = L.QF; sa.cb0 = 0; sa.fcb0 = 0; sa.frag = frag; sa.sig = sig;
   sa.gmin = XD.gmin; sa.xcount = XD.xcount; sa.xrows = XD.xrows; sa.xchanged = XD.xchanged;
-  sa.xobj = XD.xobj; sa.hcount = XD.hcount; sa.hrows = XD.hrows; sa.hbest = XD.hbest;
+  sa.hcount = XD.hcount; sa.hrows = XD.hrows; sa.hbest = XD.hbest;
   sa.hrr = XD.hrr;
-  sa.gain = gain; sa.shape = shape; sa.w = w; sa.done = done; sa.assign = assign;
-  sa.changed = changed; sa.obj = nullptr;
+  sa.gain = gain; sa.shape = shape; sa.done = done; sa.assign = assign;
+  sa.changed = changed;
   sa.nwg = L.nwg; sa.rounds = L.rounds; sa.tpc = L.tpc; sa.map_xcd = L.map_xcd; sa.lg = L.lg;
 
   WAccArgs aa;
@@ -3162,15 +3179,14 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   WFinArgs fa;
   fa.d = d; fa.K = K; fa.G = G; fa.rchunks = A.rchunks; fa.T = T_; fa.t = 0;
   fa.no_early_stop = (flags & GSRQ_NO_EARLY_STOP) ? 1 : 0;
-  fa.force_changed = 0; fa.nwg = L.nwg; fa.part = part; fa.changed = changed; fa.obj = nullptr;
+  fa.force_changed = 0; fa.nwg = L.nwg; fa.part = part; fa.changed = changed; fa.obj = objp;
   fa.seednorm = seednorm; fa.gain = gain; fa.shape = shape; fa.done = done; fa.iters = iters;
-  fa.trace = obj_trace; fa.xchanged = XD.xchanged; fa.xobj = XD.xobj; fa.kmeans = kmeans;
+  fa.trace = obj_trace; fa.xchanged = XD.xchanged; fa.kmeans = kmeans;
   fa.ovf = nullptr; fa.boff = aa.boff; fa.nwin = aa.nwin;
   // elements per lane of the accumulation and the update: lane groups of
   // d / E lanes, at most one wave
   const bool e4 = d > 128;
-  const int cpb = 256 / (d / (e4 ? 4 : 2));
-  const dim3 fgrid((unsigned)((K + cpb - 1) / cpb), (unsigned)G);
+  const dim3 fgrid((unsigned)w_fin_blocks(s), (unsigned)G);
 
   // the accumulator slice can exceed the default dynamic LDS limit
   if (hipFuncSetAttribute(e4 ? (const void*)w_accumulate_kernel<T, 4>
@@ -3260,8 +3276,6 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   } else {
     fa.force_changed = (flags & GSRQ_ASSIGN_IN) ? 0 : 1;
   }
-  sa.obj = obj_trace ? objp : nullptr;
-  fa.obj = sa.obj;
   for (int t = 1; t <= T_; ++t) {
     if ((e = w_build_frags(gain, shape, d, K, L.C, G, 0, false, done, G, sig, frag, XD, st)))
       return e;
@@ -3269,6 +3283,10 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
     fa.t = t;
     if ((e = accumulate_finalize())) return e;
     fa.force_changed = 0;
+  }
+  if (obj_trace && T_ > 0) {
+    w_trace_kernel<<<G, 64, 0, st>>>(objp, obj_trace, done, G, (int)fgrid.x, T_);
+    if ((e = launch_ok())) return e;
   }
   if (R_next) {
     // next stage's input: the rows re-encoded with the final codebook
@@ -3321,7 +3339,7 @@ gsrq_status encode(const gsrq_shape* s, const void* X, gsrq_dtype x_dtype, int64
   char* base = (char*)workspace;
   u4* frag = (u4*)(base + W.frag);
   const WDefer XD = {(float*)(base + W.gmin), (int*)(base + W.xcount), (int*)(base + W.xrows),
-                     (int*)(base + W.xchanged), (double*)(base + W.xobj),
+                     (int*)(base + W.xchanged),
                      W.hrows > W.hcount ? (int*)(base + W.hcount) : nullptr,
                      W.hrows > W.hcount ? (int*)(base + W.hrows) : nullptr,
                      W.hrows > W.hcount ? (unsigned long long*)(base + W.hbest) : nullptr,
