@@ -289,6 +289,7 @@ struct WScoreArgs {
   float* res_out;         // [N][G d] float32 residual or null
   // launch geometry
   int nwg, rounds, tpc, map_xcd, lg;
+  int table;              // w_score_table_kernel (rounds: its row blocks per workgroup)
 };
 
 // Raw elements of this lane's half of a row: the groups 2p + h (elements
@@ -1153,6 +1154,187 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
     __syncthreads();
     if (tid == 0) a.changed[(size_t)g * a.nwg + rc] = red_changed;
   }
+}
+
+// Row operands of the hi/lo contraction from a whole aligned row (d == 8 C, no
+// masked elements): as w_make_b, operand for operand.
+template <typename T, int P>
+__device__ __forceinline__ void w_make_b_full(const WRaw<T, P>& raw, int ex, int h, u4 (&bx)[P],
+                                              u4 (&blo)[P], u4& bias, float& rr,
+                                              bool& need_exact) {
+  int sr;
+  float ss = 0.f;
+  if constexpr (sizeof(T) == 2) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      bx[p] = raw.v[p];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t wj = bx[p][j];   // scalar copy before the bit cast
+        const h2 v2 = __builtin_bit_cast(h2, wj);
+        ss = __builtin_amdgcn_fdot2(v2, v2, ss, false);
+      }
+    }
+    ss += __shfl_xor(ss, 32);
+    sr = ex;
+    rr = ldexpf(ss, -ex);
+    need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
+  } else {
+    float mx = 0.f;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float v = __uint_as_float(raw.v[2 * p + (j >> 2)][j & 3]);
+        mx = fmaxf(mx, fabsf(v));
+        ss = fmaf(v, v, ss);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    ss += __shfl_xor(ss, 32);
+    int er = 0;
+    frexpf(mx, &er);
+    const int er_min = ex + SB - 15;
+    const bool tiny = er < er_min - 12;
+    er = er > er_min ? er : er_min;
+    sr = ex - er + SB;
+    rr = ldexpf(ss, SB - ex - er);
+    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      _Float16 hi[8], lo[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float v = ldexpf(__uint_as_float(raw.v[2 * p + (j >> 2)][j & 3]), SB - er);
+        hi[j] = (_Float16)v;
+        lo[j] = (_Float16)(v - (float)hi[j]);
+      }
+      bx[p] = pack_h8(hi);
+      blo[p] = pack_h8(lo);
+    }
+  }
+  rr = fminf(rr, 32768.f);
+  sr = sr < -14 ? -14 : (sr > 15 ? 15 : sr);
+  bias = h ? (u4){0u, 0u, 0u, 0u} : bias_row(sr, rr);
+}
+
+// The lane halves of a row combined: smallest distance, then the lowest
+// codeword index.
+__device__ __forceinline__ void w_combine(int best, int bt, int h, int& kstar, float& dhat) {
+  const int j = best & 15;
+  const int kidx = bt * CW + (j >> 2) * 8 + h * 4 + (j & 3);
+  const int hv = best >> 4;
+  const auto sh = __builtin_amdgcn_permlane32_swap(hv, hv, false, false);
+  const auto sk = __builtin_amdgcn_permlane32_swap(kidx, kidx, false, false);
+  const long long v0 = (long long)(int)sh[0] * 4294967296ll + (long long)(unsigned)sk[0];
+  const long long v1 = (long long)(int)sh[1] * 4294967296ll + (long long)(unsigned)sk[1];
+  const long long v = v0 < v1 ? v0 : v1;
+  dhat = __int_as_float((int)(v >> 32) << 4);
+  kstar = (int)(v & 0xffffffffll);
+}
+
+// Training pass of the hi/lo contraction at d = 64 or 128 with the codebook's
+// whole fragment table in LDS (136 KiB at d = 128, K = 256): eight waves share
+// it, each walks row blocks of 32 on its own, without a barrier, and holds the
+// next block's rows while it scores one.  Same operands, products and keys as
+// w_score_kernel.  Streamed table chunks kept a workgroup's waves in step
+// behind a barrier per chunk, its row loads and operand splits in front of
+// every round: 85 us per launch at 32768 x 1024 float32 rows, d = 128, K = 256
+// (58 us here; MFMA floor 21 us, row reads 26 us).  From 1024 rows up no size
+// measured slower than streaming (T = 6 calls at d = 128: 270 -> 250 us at
+// 1024 rows, 317 -> 301 at 4096).
+constexpr int W_TB_LDS_MAX = 150 * 1024;
+template <typename T, int C>
+__global__ void __launch_bounds__(W_THREADS, 2) w_score_table_kernel(WScoreArgs a) {
+  extern __shared__ __align__(16) u4 wtab[];
+  __shared__ int red_changed;
+  constexpr bool F16 = sizeof(T) == 2;
+  constexpr int P = w_pairs(C);
+  constexpr int QU = w_frags(C);
+  int g, rc;
+  {
+    const int id = blockIdx.x;
+    if (a.map_xcd) {
+      const int xcd = id & 7, slot = id >> 3, gpx = a.G >> 3;
+      const int j = slot % gpx;
+      rc = slot / gpx;
+      g = ((j / a.lg) * 8 + xcd) * a.lg + (j % a.lg);
+    } else {
+      g = id % a.G;
+      rc = id / a.G;
+    }
+  }
+  if (a.done && a.done[g]) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 31, h = lane >> 5;
+  constexpr int d = 8 * C;
+  const int K = a.K, tiles = a.tiles;
+  const int ex = a.sig[a.cb0 + g];
+  const T* X = (const T*)a.x + (int64_t)g * d;
+  // a.rounds row blocks per workgroup: wave w takes blocks w, w + 8, ...
+  const int64_t blk0 = (int64_t)rc * a.rounds;
+  const int64_t nblk = min((int64_t)a.rounds, (a.N + RB - 1) / RB - blk0);
+  WRaw<T, P> raw;
+  auto fetch = [&](int64_t b) {
+    const int64_t row = (blk0 + b) * RB + i;
+    raw.load(X + (row < a.N ? row : 0) * a.ldx, d, true, h);
+  };
+  if (wave < nblk) fetch(wave);
+  if (tid == 0) red_changed = 0;
+  {
+    const u4* ftab = a.frag + (size_t)(a.cb0 + g - a.fcb0) * tiles * QU * 64;
+    const int n = tiles * QU * 64;
+    constexpr int UN = 4;                 // loads in flight per thread
+    for (int e0 = tid; e0 < n; e0 += UN * W_THREADS) {
+      u4 v[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) v[u] = ftab[min(e0 + u * W_THREADS, n - 1)];
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (e0 + u * W_THREADS < n) wtab[e0 + u * W_THREADS] = v[u];
+    }
+  }
+  __syncthreads();
+  bool any_changed = false;
+  for (int64_t b = wave; b < nblk; b += W_WAVES) {
+    u4 bx[P], blo[P], bias;
+    float rr;
+    bool need_exact;
+    w_make_b_full<T, P>(raw, ex, h, bx, blo, bias, rr, need_exact);
+    // the next block's rows, in flight while this one is scored
+    __builtin_amdgcn_sched_barrier(0);
+    if (b + W_WAVES < nblk) fetch(b + W_WAVES);
+    __builtin_amdgcn_sched_barrier(0);
+    int best = 0x7fffffff, bt = 0;
+    for (int t = 0; t < tiles; ++t) {
+      const f16v c = w_tile<F16, P>(wtab + (size_t)t * QU * 64 + lane, bx, blo, bias);
+      w_take(w_tile_key(c), t, best, bt);
+    }
+    int kstar;
+    float dhat;
+    w_combine(best, bt, h, kstar, dhat);
+    const int64_t row = (blk0 + b) * RB + i;
+    const bool valid = row < a.N && h == 0;
+    // rows the key cannot decide go to the subspace's list for the exact kernel
+    const bool defer = valid && (need_exact || !(dhat <= ldexpf(rr, SA + 1)) || kstar >= K);
+    const unsigned long long fb = __ballot(defer);
+    if (fb) {
+      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(fb >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)fb, 0u));
+      int base = 0;
+      if (lane == 0) base = atomicAdd(a.xcount + g, __popcll(fb));
+      base = __shfl(base, 0);
+      if (defer) a.xrows[(size_t)g * a.N + base + rank] = (int)row;
+    }
+    if (valid && !defer) {
+      uint16_t* ap = a.assign + (size_t)g * a.N + row;
+      if (*ap != (uint16_t)kstar) any_changed = true;
+      *ap = (uint16_t)kstar;
+    }
+  }
+  if (__ballot(any_changed) && lane == 0) atomicOr(&red_changed, 1);
+  __syncthreads();
+  if (tid == 0) a.changed[(size_t)g * a.nwg + rc] = red_changed;
 }
 
 // Stage-fused encode for narrow wide rows (d <= 16) with resident fragment
@@ -2776,6 +2958,7 @@ struct WLayout {
   bool sp;              // single-pass scoring (d >= 64), then the hi/lo pass
   int Qu;
   size_t lds;
+  int tab_nwg, tab_blocks;   // w_score_table_kernel: workgroups per subspace (0: not used)
 };
 
 // Subvectors of at least 64 elements are scored in a single float16 pass
@@ -2825,6 +3008,13 @@ WLayout w_score_layout(const gsrq_shape* s, size_t x_elt, bool f16rows, bool hp 
     L.lds = 2 * (size_t)L.tpc * L.Qu * 64 * sizeof(u4);
   }
   L.nwg = (int)((row_rounds + L.rounds - 1) / L.rounds);
+  // the table kernel: one workgroup per CU in all
+  L.tab_nwg = L.tab_blocks = 0;
+  if (!L.sp && !L.resident && (s->d == 64 || s->d == 128) && L.frag_bytes <= (size_t)W_TB_LDS_MAX) {
+    const int64_t blocks = (s->N + RB - 1) / RB, wgs = std::max<int64_t>(1, 256 / G);
+    L.tab_blocks = (int)((blocks + wgs - 1) / wgs);
+    L.tab_nwg = (int)((blocks + L.tab_blocks - 1) / L.tab_blocks);
+  }
   const size_t seg = (size_t)s->d * x_elt;
   L.lg = seg < 128 ? (int)(128 / seg) : 1;
   L.map_xcd = (G % (8 * L.lg) == 0) ? 1 : 0;
@@ -2881,6 +3071,16 @@ gsrq_status w_score_launch_c(const WScoreArgs& a, const WLayout& L, hipStream_t 
       b.tpc = H.tpc;
       if ((e = w_score_launch_v<T, C, MODE, false, true>(b, H, st))) return e;
       w_listed_finish_kernel<T, MODE><<<dim3(W_LF_WGS, a.G), 256, 0, st>>>(a);
+      return launch_ok();
+    }
+  }
+  if constexpr (MODE == W_TRAIN && (C == 8 || C == 16)) {
+    if (a.table) {
+      const int lds = a.tiles * w_frags(C) * 64 * (int)sizeof(u4);
+      if (hipFuncSetAttribute((const void*)w_score_table_kernel<T, C>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+        return GSRQ_E_HIP;
+      w_score_table_kernel<T, C><<<(unsigned)(a.G * a.nwg), W_THREADS, lds, st>>>(a);
       return launch_ok();
     }
   }
@@ -3022,7 +3222,7 @@ WTrainWs w_train_ws(const gsrq_shape* s, size_t x_elt) {
   W.sig = off; off = align256(off + (size_t)G * sizeof(int));
   W.part = off;
   off = align256(off + (size_t)G * A.rchunks * s->K * (2 * s->d + 2) * sizeof(double));
-  W.changed = off; off = align256(off + (size_t)G * L16.nwg * sizeof(int));
+  W.changed = off; off = align256(off + (size_t)G * std::max(L16.nwg, L16.tab_nwg) * sizeof(int));
   W.obj = off; off = align256(off + 2 * (size_t)G * w_fin_blocks(s) * sizeof(double));
   W.assign = off; off = align256(off + (size_t)G * s->N * sizeof(uint16_t));
   W.done = off; off = align256(off + (size_t)G * sizeof(int));
@@ -3164,6 +3364,12 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   sa.gain = gain; sa.shape = shape; sa.done = done; sa.assign = assign;
   sa.changed = changed;
   sa.nwg = L.nwg; sa.rounds = L.rounds; sa.tpc = L.tpc; sa.map_xcd = L.map_xcd; sa.lg = L.lg;
+  // the table kernel reads whole rows with 16-byte loads
+  sa.table = L.tab_nwg > 0 && (uintptr_t)X % 16 == 0 && (ldx * (int64_t)sizeof(T)) % 16 == 0;
+  if (sa.table) {
+    sa.nwg = L.tab_nwg;
+    sa.rounds = L.tab_blocks;
+  }
 
   WAccArgs aa;
   aa.x = X; aa.ldx = ldx; aa.N = s->N; aa.d = d; aa.K = K; aa.G = G; aa.w = w;
@@ -3179,7 +3385,7 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   WFinArgs fa;
   fa.d = d; fa.K = K; fa.G = G; fa.rchunks = A.rchunks; fa.T = T_; fa.t = 0;
   fa.no_early_stop = (flags & GSRQ_NO_EARLY_STOP) ? 1 : 0;
-  fa.force_changed = 0; fa.nwg = L.nwg; fa.part = part; fa.changed = changed; fa.obj = objp;
+  fa.force_changed = 0; fa.nwg = sa.nwg; fa.part = part; fa.changed = changed; fa.obj = objp;
   fa.seednorm = seednorm; fa.gain = gain; fa.shape = shape; fa.done = done; fa.iters = iters;
   fa.trace = obj_trace; fa.xchanged = XD.xchanged; fa.kmeans = kmeans;
   fa.ovf = nullptr; fa.boff = aa.boff; fa.nwin = aa.nwin;
