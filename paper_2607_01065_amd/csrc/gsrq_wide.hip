@@ -1233,6 +1233,86 @@ __device__ __forceinline__ void w_combine(int best, int bt, int h, int& kstar, f
   kstar = (int)(v & 0xffffffffll);
 }
 
+// One tile of a scan over a table in LDS: the tile's hi/lo chain (as w_tile)
+// into acc, with the previous tile's keys taken from `prev` between the MFMAs
+// and the fragments read two pairs ahead across the tile border: pair p + 2 of
+// this tile, then pairs 0 and 1 of the next (tn), which are left in fh, fl.
+template <bool F16, int P>
+__device__ __forceinline__ void w_scan_step(const u4* ta, const u4* tn, const u4 (&bx)[P],
+                                            const u4 (&blo)[P], u4 bias, u4 (&fh)[2], u4 (&fl)[2],
+                                            f16v& acc, const f16v& prev, int tprev, int& best,
+                                            int& bt) {
+  constexpr int MASK = ~15, KV = 16 / P;
+  u4 H[P + 2], L[P + 2];
+  H[0] = fh[0]; H[1] = fh[1];
+  L[0] = fl[0]; L[1] = fl[1];
+  const u4 fb = ta[P * 64];
+  int m = 0x7fffffff;
+  f16v c = {};
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const u4* tq = p + 2 < P ? ta + (p + 2) * 64 : tn + (p + 2 - P) * 64;
+    H[p + 2] = tq[0];
+    L[p + 2] = tq[(P + 1) * 64];
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h8(H[p]), as_h8(bx[p]), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h8(L[p]), as_h8(bx[p]), c, 0, 0, 0);
+    if (!F16) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h8(H[p]), as_h8(blo[p]), c, 0, 0, 0);
+#pragma unroll
+    for (int j = KV * p; j < KV * p + KV; j += 2)
+      m = min(min(m, (__float_as_int(prev[j]) & MASK) | j),
+              (__float_as_int(prev[j + 1]) & MASK) | (j + 1));
+  }
+  c = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_h8(fb), as_h8(bias), c, 0, 0, 0);
+  w_take(m, tprev, best, bt);
+  acc = c;
+  fh[0] = H[P]; fh[1] = H[P + 1];
+  fl[0] = L[P]; fl[1] = L[P + 1];
+  // the schedule: per pair its MFMAs, the reads ahead, its share of the keys
+  __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, F16 ? 1 : 2, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 3 * KV / 2, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+}
+
+// Best key and its tile over an even number of tiles held in LDS (tab: this
+// lane's entry of fragment 0), as w_tile_key and w_take tile by tile.  Two
+// accumulators alternate, so a tile's key work runs in the shadow of the next
+// tile's MFMAs instead of after its own.  Training pass at d = 128, K = 256,
+// 32768 x 1024 float32 rows: 57.8 -> 55.0 us per launch, of which about 8 us is
+// launch and table copy and the rest runs at 1.15 PFLOP/s of MFMA work, the
+// rate a large float16 matrix product reaches on this card (1.17); 12-stage
+// encode of 30011 x 1024 rows 738 -> 689 us under the profiler.
+template <bool F16, int P>
+__device__ __forceinline__ void w_scan_tiles(const u4* tab, int tiles, const u4 (&bx)[P],
+                                             const u4 (&blo)[P], u4 bias, int& best, int& bt) {
+  constexpr int TU = (2 * P + 1) * 64;      // entries of one tile
+  best = 0x7fffffff;
+  bt = 0;
+  u4 fh[2], fl[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    fh[q] = tab[q * 64];
+    fl[q] = tab[(P + 1 + q) * 64];
+  }
+  f16v c0, c1;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) c1[j] = INFINITY;   // before tile 0: never below a finite key
+#pragma unroll 1
+  for (int t = 0; t < tiles; t += 2) {
+    const u4* ta = tab + (size_t)t * TU;
+    w_scan_step<F16, P>(ta, ta + TU, bx, blo, bias, fh, fl, c0, c1, t > 0 ? t - 1 : 0, best,
+                        bt);
+    w_scan_step<F16, P>(ta + TU, t + 2 < tiles ? ta + 2 * TU : ta, bx, blo, bias, fh, fl, c1, c0,
+                        t, best, bt);
+  }
+  w_take(w_tile_key(c1), tiles - 1, best, bt);
+}
+
 // Training pass of the hi/lo contraction at d = 64 or 128 with the codebook's
 // whole fragment table in LDS (136 KiB at d = 128, K = 256): eight waves share
 // it, each walks row blocks of 32 on its own, without a barrier, and holds the
@@ -1240,7 +1320,7 @@ __device__ __forceinline__ void w_combine(int best, int bt, int h, int& kstar, f
 // w_score_kernel.  Streamed table chunks kept a workgroup's waves in step
 // behind a barrier per chunk, its row loads and operand splits in front of
 // every round: 85 us per launch at 32768 x 1024 float32 rows, d = 128, K = 256
-// (58 us here; MFMA floor 21 us, row reads 26 us).  From 1024 rows up no size
+// (58 us here).  From 1024 rows up no size
 // measured slower than streaming (T = 6 calls at d = 128: 270 -> 250 us at
 // 1024 rows, 317 -> 301 at 4096).
 constexpr int W_TB_LDS_MAX = 150 * 1024;
@@ -1305,11 +1385,8 @@ __global__ void __launch_bounds__(W_THREADS, 2) w_score_table_kernel(WScoreArgs 
     __builtin_amdgcn_sched_barrier(0);
     if (b + W_WAVES < nblk) fetch(b + W_WAVES);
     __builtin_amdgcn_sched_barrier(0);
-    int best = 0x7fffffff, bt = 0;
-    for (int t = 0; t < tiles; ++t) {
-      const f16v c = w_tile<F16, P>(wtab + (size_t)t * QU * 64 + lane, bx, blo, bias);
-      w_take(w_tile_key(c), t, best, bt);
-    }
+    int best, bt;
+    w_scan_tiles<F16, P>(wtab + lane, tiles, bx, blo, bias, best, bt);
     int kstar;
     float dhat;
     w_combine(best, bt, h, kstar, dhat);
@@ -1533,7 +1610,7 @@ __global__ void __launch_bounds__(W_THREADS, 2) w_encode_fused_kernel(WFusedArgs
 // all M stages (lane half h holds groups 2p + h of its row: elements
 // [16p + 8h, 16p + 8h + 8)), so no residual crosses HBM between stages.
 // Per stage the stage's whole fragment table is copied into LDS, every
-// tile scored (float32 operand path, two tiles' MFMA chains in flight), the
+// tile scored (float32 operand path, w_scan_tiles), the
 // row's code written, and the winning codeword subtracted in place; rows
 // the key cannot decide are re-scored in float64 by the whole wave (eq. 5
 // form over every codeword; rare).  The residual leaves the registers only
@@ -1620,7 +1697,7 @@ __global__ void __launch_bounds__(W_FW_THREADS, 1) w_encode_fused_wide_kernel(WF
       __syncthreads();
     }
     u4 bx[P], blo[P], bias;
-    float rr, eD;
+    float rr;
     bool need_exact;
     {
       WRaw<float, P> raw;
@@ -1631,34 +1708,16 @@ __global__ void __launch_bounds__(W_FW_THREADS, 1) w_encode_fused_wide_kernel(WF
         raw.v[2 * p + 1] = (u4){__float_as_uint(r[p][4]), __float_as_uint(r[p][5]),
                                 __float_as_uint(r[p][6]), __float_as_uint(r[p][7])};
       }
-      w_make_b<float, P>(raw, d, valid, ex, h, bx, blo, bias, rr, need_exact, eD);
+      w_make_b_full<float, P>(raw, ex, h, bx, blo, bias, rr, need_exact);
     }
     int best = 0x7fffffff, bt = 0;
-    for (int t = 0; t < a.tiles; t += 2) {
-      const u4* ta = wtab + (size_t)t * QU * 64 + lane;
-      const f16v c0 = w_tile<false, P>(ta, bx, blo, bias);
-      if (t + 1 < a.tiles) {
-        const f16v c1 = w_tile<false, P>(ta + QU * 64, bx, blo, bias);
-        w_take(w_tile_key(c0), t, best, bt);
-        w_take(w_tile_key(c1), t + 1, best, bt);
-      } else {
-        w_take(w_tile_key(c0), t, best, bt);
-      }
-    }
+    if (a.tiles > 1)                        // a power of two
+      w_scan_tiles<false, P>(wtab + lane, a.tiles, bx, blo, bias, best, bt);
+    else
+      w_take(w_tile_key(w_tile<false, P>(wtab + lane, bx, blo, bias)), 0, best, bt);
     int kstar;
     float dhat;
-    {
-      const int j = best & 15;
-      const int kidx = bt * CW + (j >> 2) * 8 + h * 4 + (j & 3);
-      const int hv = best >> 4;
-      const auto sh = __builtin_amdgcn_permlane32_swap(hv, hv, false, false);
-      const auto sk = __builtin_amdgcn_permlane32_swap(kidx, kidx, false, false);
-      const long long v0 = (long long)(int)sh[0] * 4294967296ll + (long long)(unsigned)sk[0];
-      const long long v1 = (long long)(int)sh[1] * 4294967296ll + (long long)(unsigned)sk[1];
-      const long long v = v0 < v1 ? v0 : v1;
-      dhat = __int_as_float((int)(v >> 32) << 4);
-      kstar = (int)(v & 0xffffffffll);
-    }
+    w_combine(best, bt, h, kstar, dhat);
     need_exact = need_exact || !(dhat <= ldexpf(rr, SA + 1)) || kstar >= K;
     unsigned long long fb = __ballot(valid && need_exact && h == 0);
     while (fb) {
