@@ -2998,6 +2998,104 @@ __global__ void __launch_bounds__(256) w_decode_gather_kernel(WDecArgs a, int C)
   w_store8<TO>(dst, acc, a.vec != 0, min(8, d - 8 * q));
 }
 
+// Decode at d = 64, 128 or 256 and K <= 256 from codewords held in LDS.  A
+// workgroup owns 64 dimensions of one subspace for up to W_DT_SLOTS x 64 rows
+// and keeps their sums in registers while it goes through the stages: a
+// stage's slice of the codebook (g s rounded to float32, 64 KiB) is written to
+// one LDS buffer while the rows gather from the other.  Sixteen lanes share a
+// row (four dimensions each); each of them holds the code of one stage, which
+// a DPP broadcast hands to the row's lanes when its turn comes, so a gather is
+// one LDS read and no code traffic.
+// Bound by LDS: a row's codeword slice is 256 bytes read (12 stages of 30011 x
+// 1024 rows: 1.47 GB, 20 us at 128 B/clk per CU) after one write of the slice
+// per workgroup.  Codewords gathered from L2 and MALL, every XCD touching
+// every subspace, took 118 us for that call against 48 here, where a subspace's
+// slices stay on one XCD.  Sums are formed as in w_decode_gather_kernel, bit for bit.
+constexpr int W_DT_THREADS = 1024;
+constexpr int W_DT_DIMS = 64;                       // dimensions per workgroup
+constexpr int W_DT_K = 256;                         // codewords, at most
+constexpr int W_DT_RG = W_DT_THREADS / 16;          // rows per slot
+constexpr int W_DT_SLOTS = 12;                      // slots of rows per workgroup, at most
+constexpr int W_DT_BUF = W_DT_K * W_DT_DIMS / 4;    // f4 per buffer
+template <typename TO, int S>
+__global__ void __launch_bounds__(W_DT_THREADS) w_decode_table_kernel(WDecArgs a, int nq) {
+  extern __shared__ __align__(16) f4 dtab[];        // [2][W_DT_BUF]
+  const int nsub = a.G * nq;
+  const int sub = blockIdx.x % nsub;
+  const int g = sub / nq, dim0 = (sub % nq) * W_DT_DIMS;
+  const int64_t r0 = (int64_t)(blockIdx.x / nsub) * a.rows_per_wg;
+  const int tid = threadIdx.x, l = tid & 15, rg = tid >> 4;
+  const int K = a.K, d = a.d;
+  const int nrows = (int)min((int64_t)a.rows_per_wg, a.N - r0);
+  constexpr int PER = W_DT_BUF / W_DT_THREADS;      // slice entries per thread
+  f4 v[PER];
+  float gk[PER];
+  // uniform bases and one 32-bit offset per thread: the registers go to the
+  // sums (codewords past K repeat the last one and are never read)
+  auto load = [&](int m) {
+    const float* gb = a.gain + ((size_t)m * a.G + g) * K;
+    const float* sb = a.shape + ((size_t)m * a.G + g) * K * d + dim0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t k = (uint32_t)min(u * W_DT_RG + rg, K - 1);
+      gk[u] = gb[k];
+      v[u] = *(const f4*)(sb + (k * (uint32_t)d + 4u * (uint32_t)l));
+    }
+  };
+  auto store = [&](f4* buf) {
+    // rounded to float32 here, before the stage sum
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) buf[u * W_DT_THREADS + tid] = gk[u] * v[u];
+  };
+  f4 acc[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) acc[s] = (f4){0.f, 0.f, 0.f, 0.f};
+  int code[S];                             // lane l: stage l of its row's group of 16
+  load(0);
+  for (int m = 0; m < a.M_use; ++m) {
+    f4* buf = dtab + (size_t)(m & 1) * W_DT_BUF;
+    if ((m & 15) == 0) {
+      // (the row index opaque, so that the rows' addresses are formed here
+      // and not kept in registers across the stages)
+      int rq = rg;
+      asm volatile("" : "+v"(rq));
+      const uint32_t* cr = a.codes + r0 * a.words;
+      const int64_t bit = ((int64_t)min(m + l, a.M_use - 1) * a.G + g) * a.b;
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        code[s] = w_read_code(cr + (uint32_t)(min(s * W_DT_RG + rq, nrows - 1) * a.words), bit,
+                              a.b);
+    }
+    store(buf);
+    if (m + 1 < a.M_use) load(m + 1);
+    // one barrier per stage: a wave that writes stage m + 2 over this buffer
+    // has passed stage m + 1's barrier, which every wave reaches only after
+    // its gathers of stage m
+    __syncthreads();
+    // (slots past the last row repeat it and are never stored)
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = __builtin_amdgcn_update_dpp(0, code[s], 0x150, 0xf, 0xf, true);
+      code[s] = __builtin_amdgcn_update_dpp(0, code[s], 0x12f, 0xf, 0xf, true);
+      acc[s] += buf[k * 16 + l];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const int r = s * W_DT_RG + rg;
+    if (r >= nrows) continue;
+    TO* dst = (TO*)a.out + (r0 + r) * a.ldo + (int64_t)g * d + dim0 + 4 * l;
+    if constexpr (sizeof(TO) == 2) {
+      typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+      *(h4*)dst = (h4){(_Float16)acc[s][0], (_Float16)acc[s][1], (_Float16)acc[s][2],
+                       (_Float16)acc[s][3]};
+    } else {
+      *(f4*)dst = acc[s];
+    }
+  }
+}
+
 // ------------------------------------------------------------- host side
 
 int w_groups(int d) { return (d + 7) / 8; }
@@ -3696,6 +3794,17 @@ gsrq_status encode(const gsrq_shape* s, const void* X, gsrq_dtype x_dtype, int64
   return GSRQ_OK;
 }
 
+// Whether the table decoder takes the call.  Filling a slice per stage and
+// workgroup is what the gather kernel does not pay: 2 stages of 32768 x 1024
+// rows measured 30 us against 26 gathered, 3 stages 33 against 34, 12 stages
+// 48 against 118; 12 stages of 1024, 2048 and 4096 rows 13.0, 14.1 and 16.0 us
+// against 12.7, 14.2 and 17.9; at K = 64 (slices near the CU) 15.6 against
+// 15.0 for 4096 rows.
+bool w_use_decode_table(const gsrq_shape* s, const WDecArgs& a) {
+  return a.vec && s->d >= W_DT_DIMS && s->K <= W_DT_K && s->K >= W_DT_K / 2 && a.M_use >= 4 &&
+         s->N * s->D >= (int64_t)1 << 22;
+}
+
 gsrq_status decode(const gsrq_shape* s, const uint32_t* codes, int32_t M_use, const float* gain,
                    const float* shape, void* Xhat, gsrq_dtype out_dtype, int64_t ldo,
                    void* stream) {
@@ -3766,6 +3875,36 @@ gsrq_status decode(const gsrq_shape* s, const uint32_t* codes, int32_t M_use, co
     }
     if (e) return e;
 #undef W_DEC
+  } else if (w_use_decode_table(s, a)) {
+    const int nq = s->d / W_DT_DIMS;                // d is a power of two here
+    const int64_t nsub = (int64_t)a.G * nq;
+    // whole rounds of one workgroup per CU, each of at most W_DT_SLOTS slots
+    const int64_t most = W_DT_SLOTS * W_DT_RG;
+    const int64_t wgs = std::max<int64_t>(1, 256 / nsub);
+    const int64_t rounds = (s->N + wgs * most - 1) / (wgs * most);
+    a.rows_per_wg = (s->N + rounds * wgs - 1) / (rounds * wgs);
+    const int slots = (int)((a.rows_per_wg + 2 * W_DT_RG - 1) / (2 * W_DT_RG)) * 2;
+    a.rows_per_wg = (int64_t)slots * W_DT_RG;
+    const int64_t blocks = nsub * ((s->N + a.rows_per_wg - 1) / a.rows_per_wg);
+    if (blocks > INT32_MAX) return GSRQ_E_UNSUPPORTED;
+    const int lds = 2 * W_DT_BUF * (int)sizeof(f4);
+    auto go = [&](auto kern) -> gsrq_status {
+      if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              lds) != hipSuccess)
+        return GSRQ_E_HIP;
+      kern<<<(unsigned)blocks, W_DT_THREADS, lds, st>>>(a, nq);
+      return launch_ok();
+    };
+    const bool h = out_dtype == GSRQ_F16;
+    static_assert(W_DT_SLOTS == 12, "a case per slot count");
+    switch (slots) {
+      case 2: return h ? go(w_decode_table_kernel<_Float16, 2>) : go(w_decode_table_kernel<float, 2>);
+      case 4: return h ? go(w_decode_table_kernel<_Float16, 4>) : go(w_decode_table_kernel<float, 4>);
+      case 6: return h ? go(w_decode_table_kernel<_Float16, 6>) : go(w_decode_table_kernel<float, 6>);
+      case 8: return h ? go(w_decode_table_kernel<_Float16, 8>) : go(w_decode_table_kernel<float, 8>);
+      case 10: return h ? go(w_decode_table_kernel<_Float16, 10>) : go(w_decode_table_kernel<float, 10>);
+      default: return h ? go(w_decode_table_kernel<_Float16, 12>) : go(w_decode_table_kernel<float, 12>);
+    }
   } else {
     const int cg = w_groups(s->d);
     const int per_block = 256 / cg;
