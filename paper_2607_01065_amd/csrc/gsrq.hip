@@ -23,6 +23,8 @@
 // sum w y, sum w x, sum w and the member count per codeword, flushed as
 // per-chunk partials and reduced in a fixed order by the update kernel.
 #include <algorithm>
+#include <memory>
+#include <new>
 
 #include "gsrq_common.h"
 #include "gsrq_wide.h"
@@ -1636,6 +1638,36 @@ __global__ void __launch_bounds__(256) check_inputs_kernel(const T* __restrict__
 
 // ------------------------------------------------------------- host side
 
+// Seed rows in range and distinct within each subspace.  Rows are marked in a
+// bit map of N bits, cleared bit by bit between subspaces (sorting a copy of
+// each subspace's rows took 0.5 ms of a call that seeds 128 x 256 codewords);
+// a copy is sorted only where the map would be large or cannot be had.
+bool seeds_valid(const int32_t* seed_rows, int64_t G, int K, int64_t N) {
+  constexpr int64_t MAP_ROWS = 1 << 24;   // 2 MiB
+  std::unique_ptr<uint64_t[]> map;
+  if (N <= MAP_ROWS) map.reset(new (std::nothrow) uint64_t[(size_t)(N + 63) / 64]());
+  std::unique_ptr<int32_t[]> copy;
+  if (!map) copy.reset(new int32_t[K]);
+  for (int64_t g = 0; g < G; ++g) {
+    const int32_t* r = seed_rows + g * K;
+    for (int k = 0; k < K; ++k)
+      if (r[k] < 0 || r[k] >= N) return false;
+    if (map) {
+      for (int k = 0; k < K; ++k) {
+        const uint64_t bit = 1ull << (r[k] & 63);
+        if (map[r[k] >> 6] & bit) return false;
+        map[r[k] >> 6] |= bit;
+      }
+      for (int k = 0; k < K; ++k) map[r[k] >> 6] = 0;
+    } else {
+      std::copy(r, r + K, copy.get());
+      std::sort(copy.get(), copy.get() + K);
+      if (std::adjacent_find(copy.get(), copy.get() + K) != copy.get() + K) return false;
+    }
+  }
+  return true;
+}
+
 // Optional launch timing (off by default): HIP events bracket every launch
 // of the instrumented kernels on the launch's own stream.
 gsrq_status check_shape(const gsrq_shape* s, bool need_m) {
@@ -1993,19 +2025,7 @@ gsrq_status gsrq_train_stage(const gsrq_shape* s, const void* X, gsrq_dtype x_dt
   const int64_t G = s->D / s->d;
   if (!(flags & GSRQ_RESUME)) {
     if (!seed_rows) return GSRQ_E_ARG;
-    for (int64_t g = 0; g < G; ++g) {
-      const int32_t* r = seed_rows + g * s->K;
-      for (int k = 0; k < s->K; ++k)
-        if (r[k] < 0 || r[k] >= s->N) return GSRQ_E_ARG;
-      // distinct within the subspace: sort a copy
-      int32_t* tmp = new int32_t[s->K];
-      memcpy(tmp, r, sizeof(int32_t) * s->K);
-      std::sort(tmp, tmp + s->K);
-      bool dup = false;
-      for (int a = 1; a < s->K; ++a) dup |= tmp[a] == tmp[a - 1];
-      delete[] tmp;
-      if (dup) return GSRQ_E_ARG;
-    }
+    if (!seeds_valid(seed_rows, G, s->K, s->N)) return GSRQ_E_ARG;
   }
   const size_t elt = x_dtype == GSRQ_F16 ? sizeof(_Float16) : sizeof(float);
   const size_t need = narrow(s) ? train_layout(s, elt).total

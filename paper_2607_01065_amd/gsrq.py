@@ -174,9 +174,15 @@ def encode_workspace_bytes(N, D, d, K, M) -> int:
 
 # ------------------------------------------------------------ torch plumbing
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t) -> Optional[int]:
@@ -184,24 +190,29 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream_handle(stream) -> Optional[int]:
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream) or None
+    if stream is not None:
+        return int(stream.cuda_stream) or None
+    # the handle of torch.cuda.current_stream(), without a Stream object
+    C = _torch()._C
+    return C._cuda_getCurrentRawStream(C._cuda_getDevice()) or None
 
 
 def _dtype_code(t) -> int:
     torch = _torch()
-    if t.dtype == torch.float16:
+    dtype = t.dtype
+    if dtype == torch.float16:
         return GSRQ_F16
-    if t.dtype == torch.float32:
+    if dtype == torch.float32:
         return GSRQ_F32
-    raise TypeError(f"unsupported dtype {t.dtype}; float16 or float32 expected")
+    raise TypeError(f"unsupported dtype {dtype}; float16 or float32 expected")
 
 
 def _rows(X):
-    if X.dim() != 2 or X.stride(1) != 1:
+    stride = X.stride()
+    if len(stride) != 2 or stride[1] != 1:
         raise ValueError("X must be a 2-D tensor with unit column stride")
-    return X.shape[0], X.shape[1], X.stride(0)
+    N, D = X.shape
+    return N, D, stride[0]
 
 
 def _need(t, name, dtypes, device, shape=None):
@@ -352,21 +363,29 @@ def prepare_codebook(gain, shape, *, stream=None) -> Prepared:
 
 
 def encode_prepared(X, prep: Prepared, *, codes=None, residual=False, stream=None):
-    """encode() with a prepared codebook (no operand-table build per call)."""
+    """encode() with a prepared codebook (no operand-table build per call).
+
+    The call of every decoding step: a few microseconds of kernel, so its
+    Python work is kept short (the code words per row come from integer
+    arithmetic, and a codes tensor made here needs no checks)."""
     torch = _torch()
-    lib = load_library()
+    lib = _lib or load_library()
     N, D, ldx = _rows(X)
     if D != prep.D:
         raise ValueError("X does not match the prepared codebook's vector length")
-    sh = make_shape(N, D, prep.d, prep.K, prep.M)
-    W = int(lib.gsrq_code_words(ctypes.byref(sh)))
+    dtype = _dtype_code(X)
+    sh = Shape(N, D, prep.d, prep.K, prep.M)
+    # gsrq_code_words: ceil(M G log2(K) / 32)
+    W = max(-(-prep.M * (D // prep.d) * (prep.K.bit_length() - 1) // 32), 1)
     if codes is None:
-        codes = torch.empty((N, max(W, 1)), dtype=torch.int32, device=X.device)
-    _need(codes, "codes", (torch.int32, torch.uint32), X.device, (N, max(W, 1)))
+        codes = torch.empty((N, W), dtype=torch.int32, device=X.device)
+    else:
+        _need(codes, "codes", (torch.int32, torch.uint32), X.device, (N, W))
     res = torch.empty((N, D), dtype=torch.float32, device=X.device) if residual else None
-    st = lib.gsrq_encode_prepared(ctypes.byref(sh), _ptr(X), _dtype_code(X), ldx, _ptr(prep.buf),
-                                  _ptr(codes), _ptr(res), _stream_handle(stream))
-    _check(st, "gsrq_encode_prepared")
+    st = lib.gsrq_encode_prepared(ctypes.byref(sh), X.data_ptr(), dtype, ldx, prep.buf.data_ptr(),
+                                  codes.data_ptr(), _ptr(res), _stream_handle(stream))
+    if st != GSRQ_OK:
+        _check(st, "gsrq_encode_prepared")
     return codes, res
 
 
