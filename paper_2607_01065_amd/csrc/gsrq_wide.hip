@@ -124,7 +124,7 @@ __host__ __device__ constexpr int w_sp_sreg(int C) {
 // ------------------------------------------------------------------ kernels
 
 // Per-codebook state the fragment launch writes besides the tables: smallest
-// gain and largest gain ([2][ncb]), and the deferred-row counters it clears.
+// gain ([ncb]), and the deferred-row counters it clears.
 struct WDeferPtrs {
   float* gmin;
   int* xcount;
@@ -132,12 +132,44 @@ struct WDeferPtrs {
   int* hcount;   // null: no single pass
 };
 
+// Error bound of the single float16 pass.  It scores hi(a) . hi(b) for a . b
+// (b = x exactly for float16 rows), so by Cauchy-Schwarz a distance is off by
+// at most
+//   E = ||lo(a)|| ||b|| + ||a|| ||lo(b)||.
+// The four norms are computed, rounded up to float16, and placed in the two
+// free slots of the bias terms with a minus sign on the row's side, so the
+// contraction itself yields every codeword's lower bound L = D~ - E and the
+// two smallest keys are lower bounds: a row is decided when the second
+// smallest L exceeds the best codeword's upper bound L + 2 E.  (The bound
+// before this, 2^-9 g ||x|| with the codebook's largest gain for every
+// other codeword, made the hi/lo pass over the listed rows take 190 us per
+// launch at 65536 x 1024 float32 rows, d = 128, K = 4096, against 79 us.)
+// A float16 at least v (rounding up by half an ulp at most is covered by the
+// factor; the sums behind v are good to 2^-16).
+__device__ __forceinline__ _Float16 w_sp_norm(float v) {
+  return (_Float16)fmaxf(v * (1.f + 0x1p-9f), 0x1p-14f);
+}
+// Added to every lower bound of a row, so that keys stay non-negative: at
+// least E for any codeword (||a|| <= 2^(SA+1) (1 + 2^-20), ||lo(a)|| <=
+// 2^-11 ||a||), in D units.
+__device__ __forceinline__ float w_sp_offset(float nb, float nlo) {
+  return ldexpf(nb, SA - 10) * 1.03f + ldexpf(nlo, SA + 1) * 1.03f;
+}
+// Row-side bias of the single pass: slots 6, 7 and the offset.
+__device__ __forceinline__ void w_sp_bias(u4& bias, int h, float nb, float nlo) {
+  if (h == 0)
+    bias[3] = pack2((_Float16)-w_sp_norm(nb), nlo > 0.f ? (_Float16)-w_sp_norm(ldexpf(nlo, 3))
+                                                        : (_Float16)0.f);
+}
+
 // Operand fragments of one 32-codeword tile (grid: tiles x codebooks, one
 // wave).  Lane = codeword c (0..31) + 32 h; lane half h covers the 8-element
 // group 2p + h of pair p.  With a_j = -2 g s_j 2^SA / sigma and
 // gg = (g / sigma)^2 2^SA, the tile's fragments are, per lane, in order:
 //   HI_p (p < P)   hi(a[16p + 8h, 16p + 8h + 8))
-//   bias           h0 [hi(gg) lo(gg) 2^SA 2^SA 0 0 0 0], h1 zero
+//   bias           h0 [hi(gg) lo(gg) 2^SA 2^SA . . e1 e2], h1 zero; e1, e2:
+//                  the single pass's error norms ||lo(a)||, ||hi(a)|| 2^-3,
+//                  rounded up (w_sp_norm); their row slots are zero elsewhere
 //   LO_p (p < P)   lo(a[16p + 8h, 16p + 8h + 8))
 // so the single-pass scoring kernel stages the first P + 1 of them only.
 // Padding codewords (k >= K) have a = 0 and a float16-max g^2 slot.  P is
@@ -186,12 +218,12 @@ __global__ void __launch_bounds__(64) w_frag_kernel(const float* __restrict__ ga
   if (t == 0 && lane == 0) {
     sig[cb] = ex;
     X.gmin[cbl] = n;
-    X.gmin[gridDim.y + cbl] = m;
     X.xcount[cbl] = 0;
     X.xchanged[cbl] = 0;
     if (X.hcount) X.hcount[cbl] = 0;
   }
   u4* out = frag + ((size_t)cbl * tiles + t) * (2 * P + 1) * 64;
+  float slo = 0.f, shi = 0.f;
   float sv[P][8];
 #pragma unroll
   for (int p = 0; p < P; ++p)
@@ -208,14 +240,21 @@ __global__ void __launch_bounds__(64) w_frag_kernel(const float* __restrict__ ga
       const int e = 16 * p + 8 * h + j;
       const float av = ldexpf(-2.f * g * ((real && e < d) ? sv[p][j] : 0.f), SA - ex);
       hi[j] = (_Float16)av;
-      lo[j] = (_Float16)(av - (float)hi[j]);
+      const float dl = av - (float)hi[j];
+      lo[j] = (_Float16)dl;
+      slo = fmaf(dl, dl, slo);
+      shi = fmaf(av, av, shi);
     }
     out[p * 64 + lane] = pack_h8(hi);
     out[(P + 1 + p) * 64 + lane] = pack_h8(lo);
   }
+  slo += __shfl_xor(slo, 32);
+  shi += __shfl_xor(shi, 32);
   const float gs = ldexpf(g, -ex);
   const float gg = ldexpf(gs * gs, SA);
-  out[P * 64 + lane] = h ? (u4){0u, 0u, 0u, 0u} : bias_codeword(real, gg);
+  u4 bias = bias_codeword(real, gg);
+  bias[3] = pack2(w_sp_norm(sqrtf(slo)), w_sp_norm(ldexpf(sqrtf(shi), -3)));
+  out[P * 64 + lane] = h ? (u4){0u, 0u, 0u, 0u} : bias;
 }
 
 // Seed shapes s_k = x_r / (||x_r|| + eps) from rows of the row-major input.
@@ -266,7 +305,7 @@ struct WScoreArgs {
   int cb0;                // codebook index (gain, shape, sig) of subspace 0: m G
   int fcb0;               // codebook index of fragment-table entry 0
   const u4* frag;         // [ncb][tiles][QF][64]
-  const float* gmin;      // [ncb] smallest gain (same indexing as frag), then [ncb] largest
+  const float* gmin;      // [ncb] smallest gain (same indexing as frag)
   int* xcount;            // [G] rows deferred to the exact kernel (reset with sigma)
   int* xrows;             // [G][N] their row indices
   int* xchanged;          // [G] exact kernel: some deferred row changed code
@@ -352,7 +391,7 @@ template <typename T, int P> struct WRaw {
 template <typename T, int P>
 __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool valid, int ex, int h,
                                          u4 (&bx)[P], u4 (&blo)[P], u4& bias, float& rr,
-                                         bool& need_exact, float& eD) {
+                                         bool& need_exact) {
   constexpr bool F16 = sizeof(T) == 2;
   int sr;
   if (F16) {
@@ -375,8 +414,6 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
     sr = ex;
     rr = ldexpf(ss, -ex);
     need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
-    // single-pass error bound in D units: 2^-10 g ||x|| 2^SA / sigma, g <= sigma
-    eD = ldexpf(sqrtf(ss), SA - 10) * (1.f + 0x1p-9f);
   } else {
     float mx = 0.f, ss = 0.f;
 #pragma unroll
@@ -401,8 +438,6 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
     sr = ex - er + SB;
     rr = ldexpf(ss, SB - ex - er);
     need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
-    // single-pass error bound in D units: 2^-9 g ||x|| 2^(SA+SB) / (sigma rho)
-    eD = ldexpf(sqrtf(ss), SA + SB - 9 - er) * (1.f + 0x1p-9f);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       _Float16 hi[8], lo[8];
@@ -454,12 +489,15 @@ __device__ __forceinline__ void w_row_group(const _Float16* xp, int e0, int d, b
 
 // The same operands loaded straight from memory (no prefetch): fewer live
 // registers for wide rows, where a workgroup scores a single round.
-template <typename T, int P>
+// SP: the single pass (norms of the operand and of its dropped part, nb and
+// nlo, and the bias terms of the lower bounds).
+template <typename T, int P, bool SP>
 __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bool valid, int ex, int h,
                                          u4 (&bx)[P], u4 (&blo)[P], u4& bias, float& rr,
-                                         bool& need_exact, float& eD) {
+                                         bool& need_exact, float& nb, float& nlo) {
   constexpr bool F16 = sizeof(T) == 2;
   int sr;
+  float rr_sp = 0.f;
   if constexpr (F16) {
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     float ss = 0.f;
@@ -489,8 +527,12 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     sr = ex;
     rr = ldexpf(ss, -ex);
     need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
-    // single-pass error bound in D units: 2^-10 g ||x|| 2^SA / sigma, g <= sigma
-    eD = ldexpf(sqrtf(ss), SA - 10) * (1.f + 0x1p-9f);
+    nb = sqrtf(ss);
+    nlo = 0.f;
+    if constexpr (SP) {
+      rr_sp = w_sp_offset(nb, nlo);
+      need_exact = need_exact || !(nb < 60000.f);   // the norm's float16 slot
+    }
   } else if constexpr (P <= 8) {
     // pass 1: the row's scale, from vector loads (element loads came back a
     // few at a time and made this the slowest part of a float32-row launch)
@@ -527,8 +569,8 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     sr = ex - er + SB;
     rr = ldexpf(ss, SB - ex - er);
     need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
-    // single-pass error bound in D units: 2^-9 g ||x|| 2^(SA+SB) / (sigma rho)
-    eD = ldexpf(sqrtf(ss), SA + SB - 9 - er) * (1.f + 0x1p-9f);
+    nb = ldexpf(sqrtf(ss), SB - er);
+    float sl = 0.f;                       // ||lo(b)||^2
     // pass 2 re-reads the row (cache hits): holding pass 1's values across
     // the reduction would take 8 P registers per row block
     asm volatile("" ::: "memory");
@@ -542,7 +584,9 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
         for (int j = 0; j < 8; ++j) {
           const float v = ldexpf(xv[j], SB - er);
           hi[j] = (_Float16)v;
-          lo[j] = (_Float16)(v - (float)hi[j]);
+          const float dl = v - (float)hi[j];
+          lo[j] = (_Float16)dl;
+          if constexpr (SP) sl = fmaf(dl, dl, sl);
         }
         bx[p] = pack_h8(hi);
         blo[p] = pack_h8(lo);
@@ -551,6 +595,10 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     };
     if (vec) split_pass(std::true_type{});
     else split_pass(std::false_type{});
+    if constexpr (SP) {
+      nlo = sqrtf(sl + __shfl_xor(sl, 32));
+      rr_sp = w_sp_offset(nb, nlo);
+    }
     } else {
     // wider rows (d = 256): element loads keep the registers of a pass low
     // pass 1: the row's scale; pass 2 re-reads the (cached) row and splits it
@@ -580,8 +628,8 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     sr = ex - er + SB;
     rr = ldexpf(ss, SB - ex - er);
     need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
-    // single-pass error bound in D units: 2^-9 g ||x|| 2^(SA+SB) / (sigma rho)
-    eD = ldexpf(sqrtf(ss), SA + SB - 9 - er) * (1.f + 0x1p-9f);
+    nb = ldexpf(sqrtf(ss), SB - er);
+    float sl = 0.f;                       // ||lo(b)||^2
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int e0 = 16 * p + 8 * h;
@@ -592,15 +640,23 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
         const float x = (valid && e < d) ? (float)xp[e < d ? e : 0] : 0.f;
         const float v = ldexpf(x, SB - er);
         hi[j] = (_Float16)v;
-        lo[j] = (_Float16)(v - (float)hi[j]);
+        const float dl = v - (float)hi[j];
+        lo[j] = (_Float16)dl;
+        if constexpr (SP) sl = fmaf(dl, dl, sl);
       }
       bx[p] = pack_h8(hi);
       blo[p] = pack_h8(lo);
     }
+    if constexpr (SP) {
+      nlo = sqrtf(sl + __shfl_xor(sl, 32));
+      rr_sp = w_sp_offset(nb, nlo);
+    }
     }
   rr = fminf(rr, 32768.f);
   sr = sr < -14 ? -14 : (sr > 15 ? 15 : sr);
-  bias = h ? (u4){0u, 0u, 0u, 0u} : bias_row(sr, rr);
+  // (the offset rides in the row's own term, 2^SA rr)
+  bias = h ? (u4){0u, 0u, 0u, 0u} : bias_row(sr, SP ? fminf(rr + ldexpf(rr_sp, -SA), 65000.f) : rr);
+  if constexpr (SP) w_sp_bias(bias, h, nb, nlo);
 }
 
 // Distances of one tile: the MFMA chain over the tile's fragments at `ta`
@@ -847,7 +903,7 @@ __device__ __forceinline__ void w_put_code(uint32_t* wp, int64_t bit, int b, int
 // table is streamed (staging registers).
 // SP (single pass, d >= 64): P + 1 MFMAs per tile on the float16 operands
 // (w_tile_sp); the two smallest keys of every row are kept, and a row whose
-// second-best distance lies within twice the error bound of its best (or
+// second-best lower bound does not exceed the best one's upper bound (or
 // whose keys cannot separate a 1e-4 margin) is listed for the hi/lo pass
 // instead of being decided here.
 // IND (indirect, the hi/lo pass after SP): the rows are the subspace's
@@ -955,17 +1011,16 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
     int64_t row[R];
     const T* xp[R];
     u4 bx[R][P], blo[R][P], bias[R];
-    float rr[R], eD[R];
+    float rr[R], nb[R], nlo[R];
     bool need_exact[R];
     auto make_block = [&](int r) {
       row[r] = row_of(rd, r, valid[r]);
       xp[r] = row_ptr(row[r]);
       if (PREFETCH)
-        w_make_b<T, P>(raw, d, valid[r], ex, h, bx[r], blo[r], bias[r], rr[r], need_exact[r],
-                       eD[r]);
+        w_make_b<T, P>(raw, d, valid[r], ex, h, bx[r], blo[r], bias[r], rr[r], need_exact[r]);
       else
-        w_make_b_direct<T, P>(xp[r], d, vec, valid[r], ex, h, bx[r], blo[r], bias[r], rr[r],
-                              need_exact[r], eD[r]);
+        w_make_b_direct<T, P, SP>(xp[r], d, vec, valid[r], ex, h, bx[r], blo[r], bias[r], rr[r],
+                                  need_exact[r], nb[r], nlo[r]);
     };
     make_block(0);
     if constexpr (R == 2) make_block(1);
@@ -1064,21 +1119,24 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
         dhat = __int_as_float((int)(v >> 32) << 4);
         kstar = (int)(v & 0xffffffffll);
         if (SP) {
-          // second smallest over both halves: med3(b0, b1, min(s0, s1)); a
-          // row is decided when it lies beyond twice the error bound (the
-          // single-pass bound, float32 accumulation and key truncation)
-          // The bound of a codeword scales with its gain (eD is the bound at
-          // g = sigma): the best's own gain on its side, the codebook's
-          // largest gain for every other codeword.
+          // the two smallest lower bounds of the row over both halves (the
+          // second: med3(b0, b1, min(s0, s1))); the row is decided when the
+          // second exceeds the best codeword's upper bound by more than
+          // float32 accumulation and key truncation can add
           const auto sb = __builtin_amdgcn_permlane32_swap(best[r], best[r], false, false);
           const auto ss2 = __builtin_amdgcn_permlane32_swap(second[r], second[r], false, false);
           const int srow = med3i(sb[0], sb[1], min(ss2[0], ss2[1]));
           const float sv = __int_as_float(srow & ~15);
-          const float gb = a.unit_gain ? 1.f : gcb[kstar < K ? kstar : K - 1];
-          const float gx = a.unit_gain ? 1.f : a.gmin[a.G + (cb - a.fcb0)];
-          const float md = ldexpf(eD[r] * (gb + gx), -ex) * 1.0625f +
-                           ldexpf(dhat + ldexpf(rr[r], SA + 1), -15) + 0x1p-3f;
+          // the best codeword's norms, from its bias slots
+          const int kb = kstar < K ? kstar : K - 1;
+          const uint32_t cw =
+              ((const uint32_t*)(ftab + ((size_t)(kb >> 5) * a.QF + P) * 64 + (kb & 31)))[3];
+          const float e1 = (float)__builtin_bit_cast(_Float16, (uint16_t)cw);
+          const float e2 = (float)__builtin_bit_cast(_Float16, (uint16_t)(cw >> 16));
+          const float eb = (e1 * nb[r] + 8.f * e2 * nlo[r]) * (1.f + 0x1p-8f);
+          const float md = 2.f * eb + ldexpf(dhat + ldexpf(rr[r], SA + 1), -15) + 0x1p-3f;
           ambiguous = !(sv - dhat > md);
+          dhat = dhat + eb - w_sp_offset(nb[r], nlo[r]);   // the distance itself
         }
       }
       if (IND) {
@@ -1504,8 +1562,7 @@ __global__ void __launch_bounds__(W_THREADS, 2) w_encode_fused_kernel(WFusedArgs
       u4 bx[1], blo[1], bias;
       float rr;
       bool need_exact;
-      float eD;
-      w_make_b<float, 1>(raw, d, valid, ex, h, bx, blo, bias, rr, need_exact, eD);
+      w_make_b<float, 1>(raw, d, valid, ex, h, bx, blo, bias, rr, need_exact);
       int best = 0x7fffffff, bt = 0;
       for (int t = 0; t < a.tiles; t += 2) {
         const u4* ta = wtab + (size_t)t * QU * 64 + lane;
@@ -3260,7 +3317,7 @@ gsrq_status w_score_launch(const WScoreArgs& a, const WLayout& L, hipStream_t st
 // Deferred-row state of the G codebooks a scoring launch uses: smallest
 // gains, row lists and what the exact kernel adds to the stop test.
 struct WDefer {
-  float* gmin;      // [G] smallest gains, then [G] largest
+  float* gmin;      // [G] smallest gains
   int* xcount;      // [G]
   int* xrows;       // [G][N]
   int* xchanged;    // [G]
@@ -3368,7 +3425,7 @@ WTrainWs w_train_ws(const gsrq_shape* s, size_t x_elt) {
   const WAccLayout A = w_acc_layout(s);
   size_t off = 0;
   W.frag = off; off = align256(off + (size_t)G * L16.frag_bytes);
-  W.gmin = off; off = align256(off + 2 * (size_t)G * sizeof(float));
+  W.gmin = off; off = align256(off + (size_t)G * sizeof(float));
   W.xcount = off; off = align256(off + (size_t)G * sizeof(int));
   W.xrows = off; off = align256(off + (size_t)G * s->N * sizeof(int));
   W.xchanged = off; off = align256(off + (size_t)G * sizeof(int));
@@ -3429,7 +3486,7 @@ WEncWs w_encode_ws(const gsrq_shape* s) {
     // buffers and no deferred-row lists
     const size_t ncb = (size_t)s->M * G;
     W.frag = off; off = align256(off + ncb * L.frag_bytes);
-    W.gmin = off; off = align256(off + 2 * ncb * sizeof(float));
+    W.gmin = off; off = align256(off + ncb * sizeof(float));
     W.xcount = off; off = align256(off + ncb * sizeof(int));
     W.xrows = off;
     W.xchanged = off; off = align256(off + ncb * sizeof(int));
@@ -3440,7 +3497,7 @@ WEncWs w_encode_ws(const gsrq_shape* s) {
     return W;
   }
   W.frag = off; off = align256(off + (size_t)G * L.frag_bytes);
-  W.gmin = off; off = align256(off + 2 * (size_t)G * sizeof(float));
+  W.gmin = off; off = align256(off + (size_t)G * sizeof(float));
   W.xcount = off; off = align256(off + (size_t)G * sizeof(int));
   W.xrows = off; off = align256(off + (size_t)G * s->N * sizeof(int));
   W.xchanged = off; off = align256(off + (size_t)G * sizeof(int));

@@ -57,3 +57,32 @@ def test_listed_rows_objective_codes_residual(d, K, pad, dtype):
         ref = Xg - g64[g][k_enc[:, g], None] * s64[g][k_enc[:, g]]
         got = res[:, g * d:(g + 1) * d].cpu().numpy()
         assert np.max(np.abs(got - ref)) <= 2.0 ** -23 * np.max(np.abs(Xg) + np.abs(ref))
+
+
+@pytest.mark.parametrize("d,K,dtype", [
+    (64, 1024, torch.float16), (128, 1024, torch.float32), (128, 2048, torch.float16), (256, 1024, torch.float32),
+])
+def test_single_pass_bounds_over_wide_scales(d, K, dtype):
+    """Gains over two decades, rows from well below to far above them, rows
+    on top of codewords, duplicated codewords and zero rows: no row is decided
+    wrongly above the margin, and exact ties go to the lowest index."""
+    N, G = 4096, 2
+    rng = np.random.default_rng(d + K)
+    shape = rng.standard_normal((1, G, K, d))
+    shape = (shape / np.linalg.norm(shape, axis=-1, keepdims=True)).astype(np.float32)
+    gain = rng.lognormal(0.0, 1.0, (1, G, K)).astype(np.float32)
+    gain[0, :, K // 2:K // 2 + 8] = gain[0, :, :8]           # codewords 0..7 again at K / 2
+    shape[0, :, K // 2:K // 2 + 8] = shape[0, :, :8]
+    X = rng.standard_normal((N, G, d)) * 2.0 ** rng.uniform(-6, 6, (N, G, 1)) / np.sqrt(d)
+    X[:K // 2] = (gain[0, :, :K // 2, None] * shape[0, :, :K // 2]).transpose(1, 0, 2)
+    X[-16:] = 0.0
+    Xd = torch.from_numpy(X.reshape(N, G * d)).to(dtype).cuda()
+    codes, _ = B.encode(Xd, torch.from_numpy(gain).cuda(), torch.from_numpy(shape).cuda())
+    k = O.unpack_codes(codes.cpu().numpy().view(np.uint32), 1, G, K)[:, 0]
+    X64 = Xd.double().cpu().numpy()
+    for g in range(G):
+        Xg = X64[:, g * d:(g + 1) * d]
+        S = O.gskm_scores(Xg, gain[0, g], shape[0, g])
+        clear = O.assignment_margin(Xg, gain[0, g], shape[0, g]) > 1e-4
+        assert np.array_equal(k[clear, g], np.argmax(S, axis=1)[clear])
+        assert np.all(k[:8, g] == np.arange(8))              # equal codewords: the lower index
