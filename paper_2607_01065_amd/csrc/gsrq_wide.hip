@@ -2312,6 +2312,106 @@ __global__ void __launch_bounds__(256) w_bucket_scatter_kernel(const uint16_t* _
     srt[atomicAdd(&cur[asg[r]], 1)] = (int)r;
 }
 
+// The same counting sort in one launch, a workgroup per subspace, for the row
+// counts and codebooks whose sorted row numbers fit its LDS as 16-bit values:
+// a thread keeps the codes it has read (W_B1_PER, two to a register), the
+// histogram's scan gives the offsets, the rows are placed in LDS and leave in
+// one coalesced pass.  The three launches above cost 5 us each at least and, at
+// K = 4096, the traffic of their per-chunk counts (44 us at 65536 x 1024 rows, 26
+// us here); LDS atomics of one workgroup are what bounds this one.
+constexpr int W_B1_THREADS = 1024;
+constexpr int W_B1_ROWS = 65536;                  // rows at most
+constexpr int W_B1_PER = W_B1_ROWS / W_B1_THREADS;
+constexpr int W_B1_KMAX = 4096;
+// Training calls of four iterations, three launches : one (d = 128, us): 65536 x
+// 1024 rows 3445 : 3362 (K = 4096), 1414 : 1422 (K = 1024); 65536 x 128 rows,
+// K = 2048, 570 : 553; 16384 x 1024 rows 1276 : 1206 (K = 4096), 557 : 546 (K =
+// 1024); K = 256: 463 : 472 at 32768 x 1024 rows, 248 : 238 at 8192.
+inline bool w_bucket_one(int64_t N, int K) {
+  return N <= W_B1_ROWS && K <= W_B1_KMAX && (K >= 2048 || N <= 16384);
+}
+__global__ void __launch_bounds__(W_B1_THREADS) w_bucket_one_kernel(
+    const uint16_t* __restrict__ assign, int N, int K, const int* __restrict__ done,
+    int* __restrict__ boff, int* __restrict__ sorted, int nwin, int* __restrict__ wk) {
+  extern __shared__ int hist[];                   // [K], then the sorted rows (16 bits each)
+  __shared__ int wsum[W_B1_THREADS / 64];
+  const int g = blockIdx.x;
+  if (done && done[g]) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint16_t* rows = (uint16_t*)(hist + K);
+  for (int k = tid; k < K; k += W_B1_THREADS) hist[k] = 0;
+  int* wkg = wk ? wk + (size_t)g * nwin : nullptr;
+  if (wkg)
+    for (int i = tid; i < nwin; i += W_B1_THREADS) wkg[i] = -1;
+  const uint16_t* asg = assign + (size_t)g * N;
+  // slot u of a thread: the eight rows from 8 (u W_B1_THREADS + tid)
+  u4 code[W_B1_PER / 8];
+  const bool vec = N % 8 == 0 && (uintptr_t)asg % 16 == 0;
+#pragma unroll
+  for (int u = 0; u < W_B1_PER / 8; ++u) {
+    const int r0 = 8 * (u * W_B1_THREADS + tid);
+    code[u] = (u4){0u, 0u, 0u, 0u};
+    if (8 * u * W_B1_THREADS >= N) continue;      // uniform
+    if (vec) {
+      code[u] = *(const u4*)(asg + min(r0, N - 8));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        code[u][j] = (uint32_t)asg[min(r0 + 2 * j, N - 1)] |
+                     ((uint32_t)asg[min(r0 + 2 * j + 1, N - 1)] << 16);
+      asm volatile("" ::: "memory");              // bounds the registers
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < W_B1_PER / 8; ++u) {
+    const int r0 = 8 * (u * W_B1_THREADS + tid);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (r0 + j < N) atomicAdd(&hist[(code[u][j >> 1] >> (16 * (j & 1))) & 0xffff], 1);
+  }
+  __syncthreads();
+  // thread tid owns bins [b, e): exclusive scan over the workgroup
+  const int per = (K + W_B1_THREADS - 1) / W_B1_THREADS;
+  const int b = min(K, tid * per), e = min(K, b + per);
+  int tot = 0;
+  for (int k = b; k < e; ++k) tot += hist[k];
+  int inc = tot;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(inc, off);
+    if (lane >= off) inc += v;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int base = inc - tot;
+  for (int w2 = 0; w2 < wave; ++w2) base += wsum[w2];
+  int* bo = boff + (size_t)g * (K + 1);
+  for (int k = b; k < e; ++k) {
+    const int n = hist[k];
+    bo[k] = base;
+    hist[k] = base;
+    // the windows that codeword k's members past its first W_SORT_Q meet
+    if (wkg && n > W_SORT_Q)
+      for (int i = (base + W_SORT_Q) / W_SORT_Q; i <= (base + n - 1) / W_SORT_Q; ++i) wkg[i] = k;
+    base += n;
+  }
+  if (tid == 0) bo[K] = N;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < W_B1_PER / 8; ++u) {
+    const int r0 = 8 * (u * W_B1_THREADS + tid);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (r0 + j < N)
+        rows[atomicAdd(&hist[(code[u][j >> 1] >> (16 * (j & 1))) & 0xffff], 1)] =
+            (uint16_t)(r0 + j);
+  }
+  __syncthreads();
+  int* out = sorted + (size_t)g * N;
+  for (int r = tid; r < N; r += W_B1_THREADS) out[r] = rows[r];
+}
+
 // Value of another lane by a DPP move (the VALU's own lane crossing).
 template <int CTRL> __device__ __forceinline__ float w_dpp(float v) {
   return __int_as_float(
@@ -3621,19 +3721,31 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
         const int64_t bch = w_bucket_rows(s->N, K);
         const int bchunks = (int)((s->N + bch - 1) / bch);
         int* bcnt = (int*)(base + W.bcnt);
-        w_bucket_count_kernel<<<dim3(bchunks, G), 256, (size_t)K * sizeof(int), st>>>(
-            assign, s->N, K, bch, aa.done, bcnt);
-        const size_t slds = (size_t)bchunks * K * sizeof(int);   // <= 128 KiB
-        if (slds > 65536 &&
-            hipFuncSetAttribute((const void*)w_bucket_scan_kernel,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)slds) != hipSuccess)
-          return GSRQ_E_HIP;
-        w_bucket_scan_kernel<<<G, 1024, slds, st>>>(s->N, K, bchunks, aa.done, bcnt,
-                                                    (int*)(base + W.boff), aa.nwin,
-                                                    (int*)aa.wk);
-        w_bucket_scatter_kernel<<<dim3(bchunks, G), 256, (size_t)K * sizeof(int), st>>>(
-            assign, s->N, K, bch, aa.done, bcnt, (int*)(base + W.sorted));
+        const size_t one_lds = (size_t)K * sizeof(int) + (size_t)s->N * sizeof(uint16_t);
+        if (w_bucket_one(s->N, K)) {
+          if (one_lds > 65536 &&
+              hipFuncSetAttribute((const void*)w_bucket_one_kernel,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)one_lds) != hipSuccess)
+            return GSRQ_E_HIP;
+          w_bucket_one_kernel<<<G, W_B1_THREADS, one_lds, st>>>(
+              assign, (int)s->N, K, aa.done, (int*)(base + W.boff), (int*)(base + W.sorted),
+              aa.nwin, (int*)aa.wk);
+        } else {
+          w_bucket_count_kernel<<<dim3(bchunks, G), 256, (size_t)K * sizeof(int), st>>>(
+              assign, s->N, K, bch, aa.done, bcnt);
+          const size_t slds = (size_t)bchunks * K * sizeof(int);   // <= 128 KiB
+          if (slds > 65536 &&
+              hipFuncSetAttribute((const void*)w_bucket_scan_kernel,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)slds) != hipSuccess)
+            return GSRQ_E_HIP;
+          w_bucket_scan_kernel<<<G, 1024, slds, st>>>(s->N, K, bchunks, aa.done, bcnt,
+                                                      (int*)(base + W.boff), aa.nwin,
+                                                      (int*)aa.wk);
+          w_bucket_scatter_kernel<<<dim3(bchunks, G), 256, (size_t)K * sizeof(int), st>>>(
+              assign, s->N, K, bch, aa.done, bcnt, (int*)(base + W.sorted));
+        }
         if ((e2 = launch_ok())) return e2;
       }
       // the register kernel reads E consecutive elements with vector loads:
