@@ -1856,9 +1856,8 @@ gsrq_status train_impl(const gsrq_shape* s, const void* X, int64_t ldx, const fl
     transpose_kernel<T><<<grid_for(work, 256), 256, 0, st>>>((const T*)X, ldx, s->N, d, G, xt);
     if ((e = launch_ok())) return e;
   }
-  if ((e = fill_u32(done, G, 0u, st))) return e;
-  if ((e = fill_u32(iters, G, 0u, st))) return e;
-  if (trace && T_ > 0 && (e = fill_u32(trace, (size_t)G * T_ * 2, 0u, st))) return e;
+  if ((e = clear_train_state(done, iters, G, T_ > 0 ? trace : nullptr, (size_t)G * T_, st)))
+    return e;
 
   AssignArgs aa = {};
   aa.xt = xt; aa.N = s->N; aa.d = d; aa.K = K; aa.G = G; aa.w = w;

@@ -137,6 +137,21 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     p[i] = v;
 }
 
+// The state a training call starts from: stop flags and iteration counts [G],
+// and trace [n] (or null), all zero.  One launch: three, one per array, were
+// about 7 us of a call.
+__global__ void __launch_bounds__(256) train_state_kernel(int* done, int* iters, int G,
+                                                          double* trace, size_t n) {
+  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  const size_t step = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = i0; i < (size_t)G; i += step) {
+    done[i] = 0;
+    iters[i] = 0;
+  }
+  if (trace)
+    for (size_t i = i0; i < n; i += step) trace[i] = 0.0;
+}
+
 // --------------------------------------------------------------- host side
 
 struct TimedLaunch {
@@ -187,6 +202,13 @@ inline int grid_for(int64_t work, int block) {
 
 inline gsrq_status launch_ok() {
   return hipGetLastError() == hipSuccess ? GSRQ_OK : GSRQ_E_HIP;
+}
+
+inline gsrq_status clear_train_state(int* done, int* iters, int G, double* trace, size_t n,
+                                     hipStream_t st) {
+  const int64_t work = trace && (int64_t)n > G ? (int64_t)n : G;
+  train_state_kernel<<<grid_for(work, 256), 256, 0, st>>>(done, iters, G, trace, n);
+  return launch_ok();
 }
 
 inline gsrq_status fill_u32(void* p, size_t n, uint32_t v, hipStream_t st) {

@@ -3664,9 +3664,8 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   float* seednorm = (float*)(base + W.seednorm);
   int32_t* seeds = (int32_t*)(base + W.seeds);
   gsrq_status e;
-  if ((e = fill_u32(done, G, 0, st))) return e;
-  if ((e = fill_u32(iters, G, 0, st))) return e;
-  if (obj_trace && T_ > 0 && (e = fill_u32(obj_trace, (size_t)G * T_ * 2, 0, st))) return e;
+  if ((e = clear_train_state(done, iters, G, T_ > 0 ? obj_trace : nullptr, (size_t)G * T_, st)))
+    return e;
   const int kmeans = (flags & GSRQ_KMEANS) ? 1 : 0;
 
   WScoreArgs sa = {};
