@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <memory>
 #include <new>
+#include <type_traits>
 
 #include "gsrq_common.h"
 #include "gsrq_wide.h"
@@ -103,15 +104,19 @@ __device__ __forceinline__ void build_tiles(Tiles& tl, const float* cbg, const f
 
 // Row-side operands of one row (this lane's row).
 // F16ROWS: the row is exactly float16 (raw16), so it enters the contraction
-// as is (rho = 1, no lo part):
+// as is (rho = 1, no lo part); for codebooks with row16_direct(ex):
 //   b1 = x,  b2: h0 0, h1 [sigma sigma hi(rr) lo(rr) 0 0 0 0],
 //   rr = ||x||^2 / sigma, giving D = 2^SA dist / sigma.
 // Otherwise (float32 rows x, zero padded) rho = 2^er >= max|x| and
 //   b = x 2^SB / rho, b1 = hi(b),
 //   b2: h0 lo(b), h1 [2^SB sigma/rho (twice) hi(rr) lo(rr) 0 0 0 0],
 //   rr = 2^SB ||x||^2 / (sigma rho), giving D = 2^(SA+SB) dist / (sigma rho).
-// In both cases D <= 2^(SA+1) rr means dist <= 2 ||x||^2.  need_exact flags
-// rows whose operands leave the float16 range.
+// In both cases D <= 2^(SA+1) rr means dist <= 2 ||x||^2 (rr, and with it D,
+// carries ROW_PAD).  need_exact flags rows whose operands leave the float16
+// range.
+__device__ __forceinline__ bool row16_direct(int ex) {
+  return ex >= ROW16_EX_MIN && ex <= ROW16_EX_MAX;
+}
 template <bool F16ROWS>
 __device__ __forceinline__ void make_b(const float (&x)[8], u4 raw16, int ex, int h, h8& b1,
                                        h8& b2, float& rr, bool& need_exact, float& ss) {
@@ -128,26 +133,14 @@ __device__ __forceinline__ void make_b(const float (&x)[8], u4 raw16, int ex, in
       const h2 v = __builtin_bit_cast(h2, wj);
       ss = __builtin_amdgcn_fdot2(v, v, ss, false);
     }
-    sr = ex;
-    rr = ldexpf(ss, -ex);
-    need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
+    row16_term(ss, 8, ex, 0, sr, rr, need_exact);
   } else {
     float mx = 0.f;
     ss = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) { mx = fmaxf(mx, fabsf(x[j])); ss = fmaf(x[j], x[j], ss); }
-    int er = 0;
-    frexpf(mx, &er);
-    // a row far below the codebook's scale is scaled relative to sigma
-    // instead (keeps 2^sr in float16 range; b and rr shrink with it, D stays
-    // a positive multiple of the distance); rows so small that b would
-    // leave float16's normal range are re-scored exactly
-    const int er_min = ex + SB - 15;
-    const bool tiny = er < er_min - 12;
-    er = er > er_min ? er : er_min;
-    sr = ex - er + SB;
-    rr = ldexpf(ss, SB - ex - er);
-    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+    int er;
+    row32_term(ss, mx, 8, ex, er, sr, rr, need_exact);
     _Float16 hi[8], lo[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -403,7 +396,7 @@ __device__ int load_codebook(const float* gain, const float* shape, int d, int K
   }
   block_max_into(gm, red);
   __syncthreads();
-  return sigma_exp(__int_as_float(*red));
+  return __builtin_amdgcn_readfirstlane(sigma_exp(__int_as_float(*red)));
 }
 
 // ---------------------------------------------------------------- kernels
@@ -866,7 +859,7 @@ assign_accumulate_kernel(AssignArgs a) {
     // a subspace whose previous assignment repeated stops here (uniform)
     if (!init && chg == 0.0 && !a.no_early_stop) return;
     __syncthreads();
-    ex = sigma_exp(__int_as_float(red));
+    ex = __builtin_amdgcn_readfirstlane(sigma_exp(__int_as_float(red)));
   } else {
     if (stopped) return;   // uniform over the workgroup
     ex = load_codebook(a.gain + (size_t)g * K, a.shape + (size_t)g * K * d, d, K,
@@ -911,6 +904,8 @@ assign_accumulate_kernel(AssignArgs a) {
     if (lane == 0) v = atomicAdd(&next_blk, 1);
     return __builtin_amdgcn_readfirstlane(v);
   };
+  // one loop per form of the rows (a branch inside it measured 1.5% slower)
+  auto walk = [&](auto f16rows) {
   int rb_next = wave < nblk ? claim() : nblk;
   for (int rb = wave; rb < nblk;) {
     const int r = rb * RB + i;
@@ -926,7 +921,7 @@ assign_accumulate_kernel(AssignArgs a) {
     h8 b1, b2;
     float rr, ss;
     bool need_exact;
-    make_b<F16ROWS>(x, raw, ex, h, b1, b2, rr, need_exact, ss);
+    make_b<decltype(f16rows)::value>(x, raw, ex, h, b1, b2, rr, need_exact, ss);
     const int key = min_key(tl, b1, b2);
     float dhat;
     int kstar = reduce_rows(key, h, dhat);
@@ -965,6 +960,13 @@ assign_accumulate_kernel(AssignArgs a) {
     }
     rb = rb_next;
     rb_next = rb_after;
+  }
+  };
+  if constexpr (F16ROWS) {
+    if (row16_direct(ex)) walk(std::true_type{});
+    else walk(std::false_type{});
+  } else {
+    walk(std::false_type{});
   }
   // wave sums of the objective and changed flag
 #pragma unroll
@@ -1087,7 +1089,7 @@ __global__ void __launch_bounds__(ENC_WAVES * 64, WAVES_PER_SIMD) encode_kernel(
     for (int k = lane; k < KMAX; k += 64) m = fmaxf(m, mg[k]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    ex0 = sigma_exp(m);
+    ex0 = __builtin_amdgcn_readfirstlane(sigma_exp(m));
     build_tiles(tl, mg, ms, K, ex0, false, lane);
   } else {
     __syncthreads();   // the block counters
@@ -1156,6 +1158,7 @@ __global__ void __launch_bounds__(ENC_WAVES * 64, WAVES_PER_SIMD) encode_kernel(
     ex0 = a.sig[g];
   }
   int rb_next = rb < nblk ? claim() : nblk;
+  auto walk = [&](auto f16rows) {
   while (rb < nblk) {
     const int64_t r0 = row_begin + (int64_t)rb * RB;
     const int64_t row = r0 + i;
@@ -1181,7 +1184,7 @@ __global__ void __launch_bounds__(ENC_WAVES * 64, WAVES_PER_SIMD) encode_kernel(
       float rr, ss;
       bool need_exact;
       // after the first stage the residual is no longer float16-exact
-      if (F16IN && m == 0)
+      if (f16rows && m == 0)
         make_b<true>(x, raw, ex, h, b1, b2, rr, need_exact, ss);
       else
         make_b<false>(x, raw, ex, h, b1, b2, rr, need_exact, ss);
@@ -1229,6 +1232,16 @@ __global__ void __launch_bounds__(ENC_WAVES * 64, WAVES_PER_SIMD) encode_kernel(
     }
     rb = rb_next;
     rb_next = rb_after;
+  }
+  };
+  if constexpr (!F16IN) {
+    walk(std::false_type{});
+  } else {
+    const bool direct = row16_direct(MULTI && a.M > 1 ? a.sig[g] : ex0);
+    // (unaligned rows, one stage: the second loop would spill)
+    if constexpr (!MULTI && !VEC) walk(direct);
+    else if (direct) walk(std::true_type{});
+    else walk(std::false_type{});
   }
   __syncthreads();
   }
@@ -1339,7 +1352,7 @@ __global__ void __launch_bounds__(ENC_SMALL_WAVES * 64) encode_small_kernel(Enco
     h8 b1, b2;
     float rr, ss;
     bool need_exact;
-    if (F16IN && m == 0)
+    if (F16IN && m == 0 && row16_direct(ex))
       make_b<true>(x, raw, ex, h, b1, b2, rr, need_exact, ss);
     else
       make_b<false>(x, raw, ex, h, b1, b2, rr, need_exact, ss);

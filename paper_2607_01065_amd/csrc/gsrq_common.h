@@ -131,6 +131,64 @@ __device__ __forceinline__ u4 bias_row(int sr, float rr) {
   return (u4){pack2(c, c), pack2(h, l), pack2(cs, cs), 0u};
 }
 
+// Row term rr of the contraction, and which rows it may decide.  rr sits in a
+// float16 hi/lo pair, so it is off by up to 2^-25 and a distance by up to
+// 2^(SA-25).  ROW_PAD, the same for every codeword of a row, keeps the keys
+// from going below zero by that much: among negative keys the integer order
+// is reversed, and a row of small norm (rr below about 2^-11.7) was given the
+// worst of its good codewords.  Below row_term_min the key's own spacing
+// (2^-16 of 2^(SA+1) (rr + ROW_PAD)) or the absolute 2^-25 that a subnormal
+// low part of an operand loses (d of them, 2^(sr-44) d in rr) comes near the
+// 1e-4 of the row's energy that decides a codeword: such rows are re-scored
+// exactly.
+constexpr float ROW_PAD = 0x1p-24f;
+__device__ __forceinline__ float row_term_min(int d, int sr) {
+  return fmaxf(ROW_PAD, ldexpf((float)d, sr - 43));
+}
+// rr outside [lo, 32768), or not a number (one unsigned comparison).
+__device__ __forceinline__ bool row_term_bad(float rr, float lo) {
+  const uint32_t b = __float_as_uint(lo);
+  return !(__float_as_uint(rr) - b < __float_as_uint(32768.f) - b);
+}
+
+// Float16 rows enter the contraction as they are (bias scale sigma = 2^ex)
+// while sigma 2^-BIAS_SHIFT is a float16; below that the g^2 of small gains
+// was lost.  Codebooks of smaller gains take them as 2^q x (row16_shift) or
+// as float32 rows.
+constexpr int ROW16_EX_MIN = -8, ROW16_EX_MAX = 15;
+__device__ __forceinline__ int row16_shift(int ex) {
+  return ex < ROW16_EX_MIN ? ROW16_EX_MIN - ex : 0;
+}
+__device__ __forceinline__ u4 row16_scaled(u4 x, int q) {
+  return __builtin_bit_cast(u4, as_h8(x) * (_Float16)ldexpf(1.f, q));
+}
+__device__ __forceinline__ void row16_term(float ss, int d, int ex, int q, int& sr, float& rr,
+                                           bool& need_exact) {
+  sr = ex + q;
+  rr = ldexpf(ss, q - ex);
+  need_exact = ex > ROW16_EX_MAX || ex < -14 || row_term_bad(rr, row_term_min(d, sr));
+  rr += ROW_PAD;
+}
+
+// Float32 rows enter as 2^(SB - er) x, er from the row's largest element mx.
+__device__ __forceinline__ void row32_term(float ss, float mx, int d, int ex, int& er, int& sr,
+                                           float& rr, bool& need_exact) {
+  er = 0;
+  frexpf(mx, &er);
+  // a row far below the codebook's scale is scaled relative to sigma
+  // instead (keeps 2^sr in float16 range; b and rr shrink with it, D stays
+  // a positive multiple of the distance); rows so small that b would
+  // leave float16's normal range (mx below 2^(er_min - 13), rr below 2^-25 d)
+  // are re-scored exactly, as are rows of zeros and those with sr < -14, whose
+  // rr exceeds 2^28
+  const int er_min = ex + SB - 15;
+  er = er > er_min ? er : er_min;
+  sr = ex - er + SB;
+  rr = ldexpf(ss, SB - ex - er);
+  need_exact = row_term_bad(rr, fmaxf(ROW_PAD, ldexpf((float)d, -25)));
+  rr += ROW_PAD;
+}
+
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)

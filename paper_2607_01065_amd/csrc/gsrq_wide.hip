@@ -380,14 +380,16 @@ template <typename T, int P> struct WRaw {
 
 // Row-side operands of one row (this lane's row) for all tiles, built from
 // the raw elements; lane half h holds the groups 2p + h.
-// F16 rows (the exact float16 stage input, rho = 1):
+// F16 rows (the exact float16 stage input, rho = 1; 2^q x, and sigma 2^q for
+// sigma, in a codebook of tiny gains: row16_shift):
 //   bx[p] = x of the group;  bias (h0) [sigma sigma hi(rr) lo(rr) 0 0 0 0],
 //   rr = ||x||^2 / sigma, giving D = 2^SA dist / sigma.
 // F32 rows: rho = 2^er >= max|x|, b = x 2^SB / rho:
 //   bx[p] = hi(b), blo[p] = lo(b) of the group,
 //   bias (h0) [2^SB sigma / rho (twice) hi(rr) lo(rr) 0 0 0 0],
 //   rr = 2^SB ||x||^2 / (sigma rho), giving D = 2^(SA+SB) dist / (sigma rho).
-// need_exact flags rows whose operands leave the float16 range.
+// need_exact flags rows whose operands leave the float16 range; rr, and with
+// it D, carries ROW_PAD.
 template <typename T, int P>
 __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool valid, int ex, int h,
                                          u4 (&bx)[P], u4 (&blo)[P], u4& bias, float& rr,
@@ -411,9 +413,11 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
       }
     }
     ss += __shfl_xor(ss, 32);
-    sr = ex;
-    rr = ldexpf(ss, -ex);
-    need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
+    const int q = row16_shift(ex);
+    row16_term(ss, d, ex, q, sr, rr, need_exact);
+    if (q)
+#pragma unroll
+      for (int p = 0; p < P; ++p) bx[p] = row16_scaled(bx[p], q);
   } else {
     float mx = 0.f, ss = 0.f;
 #pragma unroll
@@ -426,18 +430,8 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
       }
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     ss += __shfl_xor(ss, 32);
-    int er = 0;
-    frexpf(mx, &er);
-    // a row far below the codebook's scale is scaled relative to sigma
-    // instead (keeps 2^sr in float16 range; b and rr shrink with it, D stays
-    // a positive multiple of the distance); rows so small that b would
-    // leave float16's normal range are re-scored exactly
-    const int er_min = ex + SB - 15;
-    const bool tiny = er < er_min - 12;
-    er = er > er_min ? er : er_min;
-    sr = ex - er + SB;
-    rr = ldexpf(ss, SB - ex - er);
-    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+    int er;
+    row32_term(ss, mx, d, ex, er, sr, rr, need_exact);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       _Float16 hi[8], lo[8];
@@ -524,10 +518,12 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
       }
     }
     ss += __shfl_xor(ss, 32);
-    sr = ex;
-    rr = ldexpf(ss, -ex);
-    need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
-    nb = sqrtf(ss);
+    const int q = row16_shift(ex);
+    row16_term(ss, d, ex, q, sr, rr, need_exact);
+    if (q)
+#pragma unroll
+      for (int p = 0; p < P; ++p) bx[p] = row16_scaled(bx[p], q);
+    nb = ldexpf(sqrtf(ss), q);
     nlo = 0.f;
     if constexpr (SP) {
       rr_sp = w_sp_offset(nb, nlo);
@@ -557,18 +553,8 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     else scale_pass(std::false_type{});
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     ss += __shfl_xor(ss, 32);
-    int er = 0;
-    frexpf(mx, &er);
-    // a row far below the codebook's scale is scaled relative to sigma
-    // instead (keeps 2^sr in float16 range; b and rr shrink with it, D stays
-    // a positive multiple of the distance); rows so small that b would
-    // leave float16's normal range are re-scored exactly
-    const int er_min = ex + SB - 15;
-    const bool tiny = er < er_min - 12;
-    er = er > er_min ? er : er_min;
-    sr = ex - er + SB;
-    rr = ldexpf(ss, SB - ex - er);
-    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+    int er;
+    row32_term(ss, mx, d, ex, er, sr, rr, need_exact);
     nb = ldexpf(sqrtf(ss), SB - er);
     float sl = 0.f;                       // ||lo(b)||^2
     // pass 2 re-reads the row (cache hits): holding pass 1's values across
@@ -616,18 +602,8 @@ __device__ __forceinline__ void w_make_b_direct(const T* xp, int d, bool vec, bo
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     ss += __shfl_xor(ss, 32);
-    int er = 0;
-    frexpf(mx, &er);
-    // a row far below the codebook's scale is scaled relative to sigma
-    // instead (keeps 2^sr in float16 range; b and rr shrink with it, D stays
-    // a positive multiple of the distance); rows so small that b would
-    // leave float16's normal range are re-scored exactly
-    const int er_min = ex + SB - 15;
-    const bool tiny = er < er_min - 12;
-    er = er > er_min ? er : er_min;
-    sr = ex - er + SB;
-    rr = ldexpf(ss, SB - ex - er);
-    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+    int er;
+    row32_term(ss, mx, d, ex, er, sr, rr, need_exact);
     nb = ldexpf(sqrtf(ss), SB - er);
     float sl = 0.f;                       // ||lo(b)||^2
 #pragma unroll
@@ -1220,6 +1196,7 @@ template <typename T, int P>
 __device__ __forceinline__ void w_make_b_full(const WRaw<T, P>& raw, int ex, int h, u4 (&bx)[P],
                                               u4 (&blo)[P], u4& bias, float& rr,
                                               bool& need_exact) {
+  constexpr int d = 16 * P;
   int sr;
   float ss = 0.f;
   if constexpr (sizeof(T) == 2) {
@@ -1235,9 +1212,11 @@ __device__ __forceinline__ void w_make_b_full(const WRaw<T, P>& raw, int ex, int
       }
     }
     ss += __shfl_xor(ss, 32);
-    sr = ex;
-    rr = ldexpf(ss, -ex);
-    need_exact = ex > 15 || ex < -14 || !(rr < 32768.f);
+    const int q = row16_shift(ex);
+    row16_term(ss, d, ex, q, sr, rr, need_exact);
+    if (q)
+#pragma unroll
+      for (int p = 0; p < P; ++p) bx[p] = row16_scaled(bx[p], q);
   } else {
     float mx = 0.f;
 #pragma unroll
@@ -1250,14 +1229,8 @@ __device__ __forceinline__ void w_make_b_full(const WRaw<T, P>& raw, int ex, int
       }
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     ss += __shfl_xor(ss, 32);
-    int er = 0;
-    frexpf(mx, &er);
-    const int er_min = ex + SB - 15;
-    const bool tiny = er < er_min - 12;
-    er = er > er_min ? er : er_min;
-    sr = ex - er + SB;
-    rr = ldexpf(ss, SB - ex - er);
-    need_exact = tiny || !(mx > 0.f) || sr < -14 || !(rr < 32768.f);
+    int er;
+    row32_term(ss, mx, d, ex, er, sr, rr, need_exact);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       _Float16 hi[8], lo[8];
