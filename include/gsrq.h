@@ -145,7 +145,11 @@ gsrq_status gsrq_encode_workspace_bytes(const gsrq_shape* s, size_t* bytes);
  *  obj_trace         [G][T] float64: entry t-1 is sum_i w_i ||x_i - c_{k_i}||^2
  *                    of iteration t's assignment against the codebook it was
  *                    made with (GSRQ_KMEANS: against the updated centroids);
- *                    entries past iters_run are 0.  Or NULL.
+ *                    entries past iters_run are 0.  Or NULL.  Formed in
+ *                    float64 and never negative for d > 8 or K > 256, where
+ *                    its error is a small share of the entry itself; for
+ *                    smaller shapes a difference of sums, good to about
+ *                    N 2^-52 of sum_i w_i ||x_i||^2.
  *  workspace         >= gsrq_train_workspace_bytes(s), 256-byte aligned.
  *
  * Initialisation (without GSRQ_RESUME): shapes are the normalised seed rows;

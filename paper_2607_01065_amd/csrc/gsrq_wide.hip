@@ -2678,7 +2678,7 @@ struct WFinArgs {
   int no_early_stop, force_changed, nwg;
   const double* part;     // [G][rchunks][K][2d+2]
   const int* changed;     // [G][nwg]
-  double* obj;            // [2][G][blocks per subspace], by iteration parity; null: no trace
+  double* obj;            // [2][G][blocks per subspace], by iteration parity (with trace)
   const float* seednorm;  // [G][K]
   float* gain;            // [G][K]
   float* shape;           // [G][K][d]
@@ -2688,8 +2688,14 @@ struct WFinArgs {
   const int* xchanged;    // [G] changed flag of the exact kernel's rows
   int kmeans;             // K-means baseline update instead of eqs. (7)(8)
   const double* ovf;      // [G][nwin][2d+2] window partials of the sorted sums, or null
-  const int* boff;        // [G][K + 1] bucket offsets (with ovf)
+  const int* boff;        // [G][K + 1] bucket offsets (with ovf or sorted)
   int nwin;
+  const void* x;          // rows, weights, assignment and bucketed rows (or null), for
+  int64_t ldx, N;         // w_block_distortion
+  int x_f16;
+  const float* w;
+  const uint16_t* assign;
+  const int* sorted;
 };
 
 // Codebook update from the chunk partials (fixed order): d / E lanes per
@@ -2697,18 +2703,67 @@ struct WFinArgs {
 // the seed shapes (a codeword without members keeps its seed row's norm).
 // Iteration: eqs. (7) and (8) with the safeguards; thread 0 of block 0
 // applies the stop test of its subspace.
-// Objective, from the same sums (no pass over the rows computes it: the
-// scoring launch that read every row and its codeword again for it took
-// @OBJ): of the assignment just made against the codebook it was made with,
-//   sum_i w_i ||x_i - g s||^2 = sum_k [sum w ||x||^2 - g_k (2 s_k . S_k - g_k ||s_k||^2 W_k)],
-// S_k = sum w x and W_k = sum w of codeword k's members, everything in
-// float64 from exact products, so the cancellation costs no accuracy.
-// K-means baseline: centroid = S_k / W_k, held as norm and direction, and
-// the trace is the distortion after the update,
-// sum_k [sum w ||x||^2 - ||S_k||^2 / W_k].  Every block leaves its codewords'
-// share in obj; the next launch's block 0 (w_trace_kernel after the last
-// iteration) adds them in block order, so the trace does not depend on the
-// order in which blocks run.
+// Objective, of the assignment just made against the codebook it was made
+// with, from the same sums (the scoring launch that read every row and its
+// codeword again for it took 115 us against 85 at 32768 x 1024 float32 rows,
+// d = 128, K = 256):
+//   sum_i w_i ||x_i - g s||^2 = sum_k [Q_k - g_k (2 s_k . S_k - g_k ||s_k||^2 W_k)],
+// Q_k = sum w ||x||^2, S_k = sum w x and W_k = sum w of codeword k's members,
+// everything in float64 from exact products.  K-means baseline: centroid =
+// S_k / W_k, held as norm and direction, and the trace is the distortion
+// after the update, sum_k [Q_k - ||S_k||^2 / W_k].  The error of a difference
+// is about 2^-53 of Q_k for each sum in it.  A block whose difference comes
+// out below W_OBJ_MIN of its energy forms its distortion from its rows
+// instead (w_block_distortion; for K-means less W_k ||m_k - c_k||^2, the
+// weighted mean m_k replacing the old centroid c_k), so the error stays a
+// small share of the trace itself where a codebook nearly reproduces the rows.
+// (Residuals instead of energies in the accumulation for every call took 13
+// us more per launch at 50021 x 1024 rows, d = 16, and 11 us at 65536 x 1024
+// float16 rows, K = 4096.)
+// Every block leaves its codewords' share in obj; the next launch's block 0
+// (w_trace_kernel after the last iteration) adds them in block order.
+constexpr double W_OBJ_MIN = 0x1p-16;
+
+// sum w ||x - g s||^2 over the rows of codewords [k0, k1) (this thread's share).
+template <typename T>
+__device__ double w_block_distortion(const WFinArgs& a, int g, int k0, int k1) {
+  const uint16_t* asg = a.assign + (size_t)g * a.N;
+  const T* X = (const T*)a.x + (int64_t)g * a.d;
+  const int tid = threadIdx.x, d = a.d;
+  double sum = 0.0;
+  // elements e0, e0 + step, ... of one member
+  auto add = [&](int64_t row, int k, int e0, int step) {
+    const T* xr = X + row * a.ldx;
+    const float* sk = a.shape + ((size_t)g * a.K + k) * d;
+    const double gk = a.gain[(size_t)g * a.K + k], w = a.w ? (double)a.w[row] : 1.0;
+    double q = 0.0;
+    for (int e = e0; e < d; e += step) {
+      const double r = fma(-gk, (double)sk[e], (double)xr[e]);
+      q = fma(r, r, q);
+    }
+    sum = fma(w, q, sum);
+  };
+  if (a.sorted) {
+    // the block's buckets, sixteen lanes per member
+    const int* bo = a.boff + (size_t)g * (a.K + 1);
+    const int m1 = bo[k1];
+    for (int m = bo[k0] + (tid >> 4); m < m1; m += 16) {
+      const int64_t row = a.sorted[(size_t)g * a.N + m];
+      add(row, asg[row], tid & 15, 16);
+    }
+  } else {
+    constexpr int UN = 8;              // codes in flight per thread
+    for (int64_t r0 = tid; r0 < a.N; r0 += UN * 256) {
+      int k[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) k[u] = asg[min(r0 + u * 256, a.N - 1)];
+#pragma unroll 1
+      for (int u = 0; u < UN; ++u)
+        if (r0 + u * 256 < a.N && k[u] >= k0 && k[u] < k1) add(r0 + u * 256, k[u], 0, 1);
+    }
+  }
+  return sum;
+}
 
 // Trace entry of iteration t of subspace g from the blocks' shares (a wave).
 __device__ __forceinline__ void w_trace_entry(const double* obj, double* trace, int g, int G,
@@ -2739,7 +2794,7 @@ __global__ void __launch_bounds__(64) w_trace_kernel(const double* obj, double* 
 
 template <int E>
 __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
-  __shared__ double red[4];
+  __shared__ double red[12];
   const int g = blockIdx.y;
   const int stopped = a.t > 0 ? a.done[g] : 0;
   // the previous iteration's trace entry (also when the subspace stopped
@@ -2790,8 +2845,9 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
 #pragma unroll
   for (int e = 0; e < E; ++e) sv[e] = sk[E * li + e];
   double gnew = (a.t == 0) ? (double)a.seednorm[(size_t)g * K + kk] : (double)*gk;
-  // this lane's share of the codeword's objective term
-  double term = active && li == 0 ? Q : 0.0;
+  // this lane's share of the codeword's objective term, and of what turns the
+  // distortion before a K-means update into the one after it
+  double term = active && li == 0 ? Q : 0.0, drop = 0.0;
   if (a.t > 0 && a.kmeans) {
     if (W > 0.0) {
       double c[E];
@@ -2800,6 +2856,12 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
       double cn = c[E - 1] * c[E - 1];
 #pragma unroll
       for (int e = E - 2; e >= 0; --e) cn = fma(c[e], c[e], cn);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const double move = fma(-gnew, sv[e], c[e]);
+        drop = fma(move, move, drop);
+      }
+      drop = active ? W * drop : 0.0;
       if (active) term -= W * cn;
       for (int off = L / 2; off > 0; off >>= 1) cn += __shfl_xor(cn, off);
       cn = sqrt(cn);
@@ -2832,18 +2894,37 @@ __global__ void __launch_bounds__(256) w_finalize_kernel(WFinArgs a) {
     for (int off = L / 2; off > 0; off >>= 1) pr += __shfl_xor(pr, off);
     gnew = fmax(0.0, pr / W);
   }
+  if (a.t > 0 && a.trace) {
+    double energy = active && li == 0 ? Q : 0.0;
+    for (int off = 32; off > 0; off >>= 1) {
+      term += __shfl_xor(term, off);
+      energy += __shfl_xor(energy, off);
+    }
+    if ((tid & 63) == 0) {
+      red[tid >> 6] = term;
+      red[4 + (tid >> 6)] = energy;
+    }
+    __syncthreads();
+    double share = red[0] + red[1] + red[2] + red[3];
+    energy = red[4] + red[5] + red[6] + red[7];
+    if (energy > 0.0 && !(share > W_OBJ_MIN * energy)) {   // uniform
+      const int k0 = blockIdx.x * (256 / L), k1 = min(K, k0 + 256 / L);
+      double part = (a.x_f16 ? w_block_distortion<_Float16>(a, g, k0, k1)
+                             : w_block_distortion<float>(a, g, k0, k1)) - drop;
+      for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+      if ((tid & 63) == 0) red[8 + (tid >> 6)] = part;
+      __syncthreads();
+      share = red[8] + red[9] + red[10] + red[11];
+    }
+    // (not fmax: a NaN stays one)
+    if (tid == 0)
+      a.obj[((size_t)(a.t & 1) * a.G + g) * gridDim.x + blockIdx.x] = share < 0.0 ? 0.0 : share;
+  }
+  // (the old codebook is read above)
   if (active) {
 #pragma unroll
     for (int e = 0; e < E; ++e) sk[E * li + e] = (float)sv[e];
     if (li == 0) *gk = (float)gnew;
-  }
-  if (a.t > 0 && a.trace) {
-    for (int off = 32; off > 0; off >>= 1) term += __shfl_xor(term, off);
-    if ((tid & 63) == 0) red[tid >> 6] = term;
-    __syncthreads();
-    if (tid == 0)
-      a.obj[((size_t)(a.t & 1) * a.G + g) * gridDim.x + blockIdx.x] =
-          red[0] + red[1] + red[2] + red[3];
   }
   if (a.t > 0 && blockIdx.x == 0 && tid < 64) {
     // stop test: the scoring workgroups' changed flags
@@ -3675,6 +3756,8 @@ gsrq_status w_train(const gsrq_shape* s, const void* X, int64_t ldx, const float
   fa.seednorm = seednorm; fa.gain = gain; fa.shape = shape; fa.done = done; fa.iters = iters;
   fa.trace = obj_trace; fa.xchanged = XD.xchanged; fa.kmeans = kmeans;
   fa.ovf = nullptr; fa.boff = aa.boff; fa.nwin = aa.nwin;
+  fa.x = X; fa.ldx = ldx; fa.N = s->N; fa.x_f16 = sizeof(T) == 2; fa.w = w; fa.assign = assign;
+  fa.sorted = aa.sorted;
   // elements per lane of the accumulation and the update: lane groups of
   // d / E lanes, at most one wave
   const bool e4 = d > 128;
