@@ -374,9 +374,10 @@ def encode_prepared(X, prep: Prepared, *, codes=None, residual=False, stream=Non
     if D != prep.D:
         raise ValueError("X does not match the prepared codebook's vector length")
     dtype = _dtype_code(X)
-    sh = Shape(N, D, prep.d, prep.K, prep.M)
-    # gsrq_code_words: ceil(M G log2(K) / 32)
-    W = max(-(-prep.M * (D // prep.d) * (prep.K.bit_length() - 1) // 32), 1)
+    d, K, M = int(prep.d), int(prep.K), int(prep.M)
+    sh = Shape(N, D, d, K, M)
+    # gsrq_code_words: ceil(M G log2(K) / 32) (invalid shapes: the call's error)
+    W = max(-(-M * (D // d) * (K.bit_length() - 1) // 32), 1) if d > 0 else 1
     if codes is None:
         codes = torch.empty((N, W), dtype=torch.int32, device=X.device)
     else:
