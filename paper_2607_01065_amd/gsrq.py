@@ -190,11 +190,19 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream_handle(stream) -> Optional[int]:
-    if stream is not None:
-        return int(stream.cuda_stream) or None
-    # the handle of torch.cuda.current_stream(), without a Stream object
+    s = _torch().cuda.current_stream() if stream is None else stream
+    return int(s.cuda_stream) or None
+
+
+def _append_stream_handle(stream) -> Optional[int]:
+    """_stream_handle for the call of every decoding step: the handle of the
+    current stream without a Stream object (a microsecond of a call's seven),
+    where this torch has the calls that give it."""
     C = _torch()._C
-    return C._cuda_getCurrentRawStream(C._cuda_getDevice()) or None
+    raw, device = getattr(C, "_cuda_getCurrentRawStream", None), getattr(C, "_cuda_getDevice", None)
+    if stream is not None or raw is None or device is None:
+        return _stream_handle(stream)
+    return raw(device()) or None
 
 
 def _dtype_code(t) -> int:
@@ -384,7 +392,7 @@ def encode_prepared(X, prep: Prepared, *, codes=None, residual=False, stream=Non
         _need(codes, "codes", (torch.int32, torch.uint32), X.device, (N, W))
     res = torch.empty((N, D), dtype=torch.float32, device=X.device) if residual else None
     st = lib.gsrq_encode_prepared(ctypes.byref(sh), X.data_ptr(), dtype, ldx, prep.buf.data_ptr(),
-                                  codes.data_ptr(), _ptr(res), _stream_handle(stream))
+                                  codes.data_ptr(), _ptr(res), _append_stream_handle(stream))
     if st != GSRQ_OK:
         _check(st, "gsrq_encode_prepared")
     return codes, res

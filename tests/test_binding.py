@@ -41,3 +41,20 @@ def test_append_refuses_shapes_through_the_library(d, K, M):
     with pytest.raises(B.GsrqError) as e:
         B.encode_prepared(torch.zeros((5, 64), dtype=torch.float16), prep, stream=_stream(0))
     assert e.value.status == B.GSRQ_E_ARG
+
+
+def test_append_stream_without_private_calls(monkeypatch):
+    lib = _Lib()
+    monkeypatch.setattr(B, "_lib", lib)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: _stream(1234))
+    prep = B.Prepared(torch.zeros(256, dtype=torch.uint8), 64, 8, 256, 1)
+    B.encode_prepared(torch.zeros((5, 64), dtype=torch.float16), prep)
+    assert lib.call[-1] == 1234
+
+
+def test_other_calls_ask_for_the_current_stream(monkeypatch):
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: _stream(77))
+    assert B._stream_handle(None) == 77
+    assert B._stream_handle(_stream(5)) == 5 and B._stream_handle(_stream(0)) is None
