@@ -364,17 +364,18 @@ template <typename T, int P> struct WRaw {
       }
     }
   }
-  // element j of pair p (as float), zero past d or for an invalid row
-  __device__ __forceinline__ float at(int p, int j, int d, int h, bool valid) const {
-    const int e = 16 * p + 8 * h + j;
-    float x;
+  // element j of pair p (as float)
+  __device__ __forceinline__ float whole(int p, int j) const {
     if (sizeof(T) == 2) {
       const uint32_t w = v[p][j >> 1];
-      x = (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> (16 * (j & 1))));
-    } else {
-      x = __uint_as_float(v[2 * p + (j >> 2)][j & 3]);
+      return (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> (16 * (j & 1))));
     }
-    return (valid && e < d) ? x : 0.f;
+    return __uint_as_float(v[2 * p + (j >> 2)][j & 3]);
+  }
+  // the same, zero past d or for an invalid row
+  __device__ __forceinline__ float at(int p, int j, int d, int h, bool valid) const {
+    const float x = whole(p, j);
+    return (valid && 16 * p + 8 * h + j < d) ? x : 0.f;
   }
 };
 
@@ -389,8 +390,8 @@ template <typename T, int P> struct WRaw {
 //   bias (h0) [2^SB sigma / rho (twice) hi(rr) lo(rr) 0 0 0 0],
 //   rr = 2^SB ||x||^2 / (sigma rho), giving D = 2^(SA+SB) dist / (sigma rho).
 // need_exact flags rows whose operands leave the float16 range; rr, and with
-// it D, carries ROW_PAD.
-template <typename T, int P>
+// it D, carries ROW_PAD.  FULL: a whole row (d == 16 P), nothing masked.
+template <typename T, int P, bool FULL = false>
 __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool valid, int ex, int h,
                                          u4 (&bx)[P], u4 (&blo)[P], u4& bias, float& rr,
                                          bool& need_exact) {
@@ -401,7 +402,7 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
     float ss = 0.f;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-      const bool live = valid && 16 * p + 8 * h < d;   // d is a multiple of 8
+      const bool live = FULL || (valid && 16 * p + 8 * h < d);   // d is a multiple of 8
       bx[p] = live ? raw.v[p] : (u4){0u, 0u, 0u, 0u};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -424,7 +425,7 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
     for (int p = 0; p < P; ++p)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float v = raw.at(p, j, d, h, valid);
+        const float v = FULL ? raw.whole(p, j) : raw.at(p, j, d, h, valid);
         mx = fmaxf(mx, fabsf(v));
         ss = fmaf(v, v, ss);
       }
@@ -437,7 +438,7 @@ __device__ __forceinline__ void w_make_b(const WRaw<T, P>& raw, int d, bool vali
       _Float16 hi[8], lo[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float v = ldexpf(raw.at(p, j, d, h, valid), SB - er);
+        const float v = ldexpf(FULL ? raw.whole(p, j) : raw.at(p, j, d, h, valid), SB - er);
         hi[j] = (_Float16)v;
         lo[j] = (_Float16)(v - (float)hi[j]);
       }
@@ -1190,65 +1191,6 @@ __global__ void __launch_bounds__(w_score_waves(C, RESIDENT, SP, IND) * 64, (RES
   }
 }
 
-// Row operands of the hi/lo contraction from a whole aligned row (d == 8 C, no
-// masked elements): as w_make_b, operand for operand.
-template <typename T, int P>
-__device__ __forceinline__ void w_make_b_full(const WRaw<T, P>& raw, int ex, int h, u4 (&bx)[P],
-                                              u4 (&blo)[P], u4& bias, float& rr,
-                                              bool& need_exact) {
-  constexpr int d = 16 * P;
-  int sr;
-  float ss = 0.f;
-  if constexpr (sizeof(T) == 2) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      bx[p] = raw.v[p];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t wj = bx[p][j];   // scalar copy before the bit cast
-        const h2 v2 = __builtin_bit_cast(h2, wj);
-        ss = __builtin_amdgcn_fdot2(v2, v2, ss, false);
-      }
-    }
-    ss += __shfl_xor(ss, 32);
-    const int q = row16_shift(ex);
-    row16_term(ss, d, ex, q, sr, rr, need_exact);
-    if (q)
-#pragma unroll
-      for (int p = 0; p < P; ++p) bx[p] = row16_scaled(bx[p], q);
-  } else {
-    float mx = 0.f;
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float v = __uint_as_float(raw.v[2 * p + (j >> 2)][j & 3]);
-        mx = fmaxf(mx, fabsf(v));
-        ss = fmaf(v, v, ss);
-      }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    ss += __shfl_xor(ss, 32);
-    int er;
-    row32_term(ss, mx, d, ex, er, sr, rr, need_exact);
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      _Float16 hi[8], lo[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float v = ldexpf(__uint_as_float(raw.v[2 * p + (j >> 2)][j & 3]), SB - er);
-        hi[j] = (_Float16)v;
-        lo[j] = (_Float16)(v - (float)hi[j]);
-      }
-      bx[p] = pack_h8(hi);
-      blo[p] = pack_h8(lo);
-    }
-  }
-  rr = fminf(rr, 32768.f);
-  sr = sr < -14 ? -14 : (sr > 15 ? 15 : sr);
-  bias = h ? (u4){0u, 0u, 0u, 0u} : bias_row(sr, rr);
-}
-
 // The lane halves of a row combined: smallest distance, then the lowest
 // codeword index.
 __device__ __forceinline__ void w_combine(int best, int bt, int h, int& kstar, float& dhat) {
@@ -1274,6 +1216,7 @@ __device__ __forceinline__ void w_scan_step(const u4* ta, const u4* tn, const u4
                                             f16v& acc, const f16v& prev, int tprev, int& best,
                                             int& bt) {
   constexpr int MASK = ~15, KV = 16 / P;
+  static_assert(P >= 2 && KV % 2 == 0, "two pairs ahead, keys in pairs");
   u4 H[P + 2], L[P + 2];
   H[0] = fh[0]; H[1] = fh[1];
   L[0] = fl[0]; L[1] = fl[1];
@@ -1411,7 +1354,7 @@ __global__ void __launch_bounds__(W_THREADS, 2) w_score_table_kernel(WScoreArgs 
     u4 bx[P], blo[P], bias;
     float rr;
     bool need_exact;
-    w_make_b_full<T, P>(raw, ex, h, bx, blo, bias, rr, need_exact);
+    w_make_b<T, P, true>(raw, d, true, ex, h, bx, blo, bias, rr, need_exact);
     // the next block's rows, in flight while this one is scored
     __builtin_amdgcn_sched_barrier(0);
     if (b + W_WAVES < nblk) fetch(b + W_WAVES);
@@ -1738,7 +1681,7 @@ __global__ void __launch_bounds__(W_FW_THREADS, 1) w_encode_fused_wide_kernel(WF
         raw.v[2 * p + 1] = (u4){__float_as_uint(r[p][4]), __float_as_uint(r[p][5]),
                                 __float_as_uint(r[p][6]), __float_as_uint(r[p][7])};
       }
-      w_make_b_full<float, P>(raw, ex, h, bx, blo, bias, rr, need_exact);
+      w_make_b<float, P, true>(raw, 16 * P, true, ex, h, bx, blo, bias, rr, need_exact);
     }
     int best = 0x7fffffff, bt = 0;
     if (a.tiles > 1)                        // a power of two
