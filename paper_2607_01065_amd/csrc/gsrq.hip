@@ -404,7 +404,9 @@ __device__ int load_codebook(const float* gain, const float* shape, int d, int K
 // X [N][ldx] -> Xt [G][N][8] (zero padded past d), same element type.
 // Bound by HBM (every element read and written once).  VEC: d == 8 with
 // 16-byte aligned rows, 16-byte accesses with TR_ITEMS rows in flight per
-// thread: 37 -> 22.7 us for 32768 x 1024 float16 rows (5.9 TB/s).
+// thread: 36.6 -> 25 us for 32768 x 1024 float16 rows (rocprofv3, rows not
+// read before; 134 MB at 5.3 TB/s, what a large copy reaches; 40.8 -> 32.7 us
+// between HIP events in a training step).
 constexpr int TR_ITEMS = 4;
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ X, int64_t ldx,

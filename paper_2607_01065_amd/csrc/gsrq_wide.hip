@@ -682,9 +682,9 @@ __device__ __forceinline__ f16v w_tile(const u4* ta, const u4 (&bx)[P], const u4
 
 // Single-pass distances of one tile: hi(a) against the row's float16
 // operand (the row itself, or hi(b) of a float32 row) per pair, then the
-// bias terms (P + 1 MFMAs instead of 2P + 1 or 3P + 1).  The dropped lo
-// parts bound the error: |D~ - D| <= 2^-10 (1 + 2^-11) sum |a_j b_j| for
-// float16 rows, 2^-9 (1 + 2^-12) sum |a_j b_j| for float32 rows.
+// bias terms (P + 1 MFMAs instead of 2P + 1 or 3P + 1).  With the norms
+// in the bias terms' free slots it is a lower bound of the distance: the
+// dropped lo parts are covered by the bound above w_sp_norm.
 template <int P>
 __device__ __forceinline__ f16v w_tile_sp(const u4* ta, const u4 (&bx)[P], u4 bias) {
   f16v acc = {};
@@ -1294,9 +1294,12 @@ __device__ __forceinline__ void w_scan_tiles(const u4* tab, int tiles, const u4 
 // w_score_kernel.  Streamed table chunks kept a workgroup's waves in step
 // behind a barrier per chunk, its row loads and operand splits in front of
 // every round: 85 us per launch at 32768 x 1024 float32 rows, d = 128, K = 256
-// (58 us here).  From 1024 rows up no size
-// measured slower than streaming (T = 6 calls at d = 128: 270 -> 250 us at
-// 1024 rows, 317 -> 301 at 4096).
+// (58 us here).  No size from 256 rows up measured slower than streaming (T = 6
+// calls at d = 128, K = 256, float32: 326 -> 296 us at 320 x 1024 rows, 333 ->
+// 303 at 1024, 709 -> 684 at 1024 x 8192; d = 64: 245 -> 231 at 320 x 1024).
+// Built for d = 64 and 128: narrower tables are resident, and at d = 256 the
+// operands and the next block of float32 rows alone would take 256 registers
+// (w_scan_step also takes a tile's keys in pairs, 16 / P of them per pair).
 constexpr int W_TB_LDS_MAX = 150 * 1024;
 template <typename T, int C>
 __global__ void __launch_bounds__(W_THREADS, 2) w_score_table_kernel(WScoreArgs a) {
@@ -3966,7 +3969,10 @@ gsrq_status encode(const gsrq_shape* s, const void* X, gsrq_dtype x_dtype, int64
 // rows measured 30 us against 26 gathered, 3 stages 33 against 34, 12 stages
 // 48 against 118; 12 stages of 1024, 2048 and 4096 rows 13.0, 14.1 and 16.0 us
 // against 12.7, 14.2 and 17.9; at K = 64 (slices near the CU) 15.6 against
-// 15.0 for 4096 rows.
+// 15.0 for 4096 rows.  At other row lengths (calls, gather : here, us): 12 stages
+// of 1024 x 4096 at d = 64 22.0 : 15.3, of 512 x 8192 at d = 128 23.4 : 23.1, 20 of
+// 8192 x 512 22.6 : 20.5, 4 of 65536 x 512 34.1 : 34.1, 5 of 30000 x 1024 at d = 256
+// 49.0 : 32.7.
 bool w_use_decode_table(const gsrq_shape* s, const WDecArgs& a) {
   return a.vec && s->d >= W_DT_DIMS && s->K <= W_DT_K && s->K >= W_DT_K / 2 && a.M_use >= 4 &&
          s->N * s->D >= (int64_t)1 << 22;
