@@ -1,6 +1,7 @@
-"""Stage-fused encode at d = 64 and 128 (single pass with candidates): equal and
-nearly equal codewords, zero gains, single tiles and the largest tables, odd
-row counts, against the float64 residual recursion stage by stage."""
+"""Stage-fused encode at d = 64 and 128 (hi/lo contraction over a stage's table in
+LDS): equal and nearly equal codewords, zero gains, single tiles and the
+largest tables, odd row counts, against the float64 residual recursion stage by
+stage."""
 import numpy as np
 import pytest
 import torch
@@ -31,10 +32,10 @@ def _check(X, gain, shape, codes):
 
 
 @pytest.mark.parametrize("d,K,M,N,dtype,pad", [
-    # the single pass with candidates (a workgroup of 256 rows and one subspace for every CU)
+    # a workgroup (256 rows of a subspace) for every CU: one row in the last, full ones, a partial block; unaligned rows
     (128, 256, 3, 127 * 256 + 1, torch.float16, 0), (128, 256, 2, 32768, torch.float32, 3),
     (64, 512, 3, 128 * 256 - 31, torch.float16, 0),
-    # the hi/lo contraction
+    # a few workgroups, single tiles (K = 32), less than a block
     (128, 256, 3, 257, torch.float16, 0), (128, 32, 2, 100, torch.float32, 0), (64, 512, 3, 300, torch.float16, 0),
     (64, 256, 5, 33, torch.float32, 0), (64, 32, 2, 31, torch.float16, 1),
 ])

@@ -49,10 +49,11 @@ def test_listed_rows_objective_codes_residual(d, K, pad, dtype):
         clear = O.assignment_margin(Xg, g64[g], s64[g]) > 1e-4
         assert np.array_equal(assign[g][clear], best[clear])
         assert np.array_equal(k_enc[clear, g], best[clear])
-        # float32 sums of d squares per row: each within (d + 8) 2^-24 of its value
+        # float64 sums of the rows' energies
         diff = Xg - g64[g][assign[g], None] * s64[g][assign[g]]
         want = float(np.sum(w.astype(np.float64) * np.sum(diff * diff, axis=1)))
-        assert abs(float(r.trace[g, 0]) - want) <= (d + 8) * 2.0 ** -24 * want
+        energy = float(np.sum(w.astype(np.float64) * np.sum(Xg * Xg, axis=1)))
+        assert abs(float(r.trace[g, 0]) - want) <= N * 2.0 ** -52 * energy
         # one float32 multiply-add per element
         ref = Xg - g64[g][k_enc[:, g], None] * s64[g][k_enc[:, g]]
         got = res[:, g * d:(g + 1) * d].cpu().numpy()
