@@ -1689,13 +1689,15 @@ __global__ void __launch_bounds__(256) check_inputs_kernel(const T* __restrict__
 // Seed rows in range and distinct within each subspace.  Rows are marked in a
 // bit map of N bits, cleared bit by bit between subspaces (sorting a copy of
 // each subspace's rows took 0.5 ms of a call that seeds 128 x 256 codewords);
-// a copy is sorted only where the map would be large or cannot be had.
+// a copy is sorted only where the map would be large or cannot be had, and
+// pairs are compared where that cannot be had either (no exception leaves a C
+// entry).
 bool seeds_valid(const int32_t* seed_rows, int64_t G, int K, int64_t N) {
   constexpr int64_t MAP_ROWS = 1 << 24;   // 2 MiB
   std::unique_ptr<uint64_t[]> map;
   if (N <= MAP_ROWS) map.reset(new (std::nothrow) uint64_t[(size_t)(N + 63) / 64]());
   std::unique_ptr<int32_t[]> copy;
-  if (!map) copy.reset(new int32_t[K]);
+  if (!map) copy.reset(new (std::nothrow) int32_t[K]);
   for (int64_t g = 0; g < G; ++g) {
     const int32_t* r = seed_rows + g * K;
     for (int k = 0; k < K; ++k)
@@ -1707,10 +1709,13 @@ bool seeds_valid(const int32_t* seed_rows, int64_t G, int K, int64_t N) {
         map[r[k] >> 6] |= bit;
       }
       for (int k = 0; k < K; ++k) map[r[k] >> 6] = 0;
-    } else {
+    } else if (copy) {
       std::copy(r, r + K, copy.get());
       std::sort(copy.get(), copy.get() + K);
       if (std::adjacent_find(copy.get(), copy.get() + K) != copy.get() + K) return false;
+    } else {
+      for (int k = 1; k < K; ++k)
+        if (std::find(r, r + k, r[k]) != r + k) return false;
     }
   }
   return true;
