@@ -28,16 +28,16 @@ METRIC = "GSRQ encode vectors/s + GSKM iter/s at 1-bit; % of MFMA / HBM roofline
 # scaled x2.000 and writes x1.000 against a 256 MiB reference copy).  Valid
 # only for the kernel source those passes measured; other workloads: null.
 TRAFFIC = {
-    "llama3_8b_layer_1bit": {"source": "gsrq.hip", "source_sha256_prefix": "7f89a9b9b381e8bf",
-                             "bytes_per_launch": 116584599},
-    "llama3_8b_cache_1bit": {"source": "gsrq.hip", "source_sha256_prefix": "7f89a9b9b381e8bf",
-                             "bytes_per_launch": 294835399},
+    "llama3_8b_layer_1bit": {"source": "gsrq.hip", "source_sha256_prefix": "ef1f057b2c9517d1",
+                             "bytes_per_launch": 116587662},
+    "llama3_8b_cache_1bit": {"source": "gsrq.hip", "source_sha256_prefix": "ef1f057b2c9517d1",
+                             "bytes_per_launch": 294835764},
     "large_codebook_d128": {"source": "gsrq_wide.hip", "source_sha256_prefix": "de33a0383ae61ea5",
-                            "bytes_per_launch": 332381354},
+                            "bytes_per_launch": 332169351},
     "paper_rates_d128": {"source": "gsrq_wide.hip", "source_sha256_prefix": "bffb1448b9cbf9bf",
                          "bytes_per_launch": 141466069},
     "rate_sweep_d16": {"source": "gsrq_wide.hip", "source_sha256_prefix": "de33a0383ae61ea5",
-                       "bytes_per_launch": 290004771},
+                       "bytes_per_launch": 290007796},
     "decode_attention_1bit": {"source": "gsrq_attn.hip", "source_sha256_prefix": "123617164b1ac182",
                               "bytes_per_launch": 89763895},
     "decode_attention_075bit": {"source": "gsrq_attn.hip",

@@ -102,6 +102,11 @@ __device__ __forceinline__ void build_tiles(Tiles& tl, const float* cbg, const f
   }
 }
 
+// Whether float16 rows enter as they are; as float32 rows otherwise.
+__device__ __forceinline__ bool row16_direct(int ex) {
+  return ex >= ROW16_EX_MIN && ex <= ROW16_EX_MAX;
+}
+
 // Row-side operands of one row (this lane's row).
 // F16ROWS: the row is exactly float16 (raw16), so it enters the contraction
 // as is (rho = 1, no lo part); for codebooks with row16_direct(ex):
@@ -114,9 +119,6 @@ __device__ __forceinline__ void build_tiles(Tiles& tl, const float* cbg, const f
 // In both cases D <= 2^(SA+1) rr means dist <= 2 ||x||^2 (rr, and with it D,
 // carries ROW_PAD).  need_exact flags rows whose operands leave the float16
 // range.
-__device__ __forceinline__ bool row16_direct(int ex) {
-  return ex >= ROW16_EX_MIN && ex <= ROW16_EX_MAX;
-}
 template <bool F16ROWS>
 __device__ __forceinline__ void make_b(const float (&x)[8], u4 raw16, int ex, int h, h8& b1,
                                        h8& b2, float& rr, bool& need_exact, float& ss) {
@@ -405,8 +407,8 @@ __device__ int load_codebook(const float* gain, const float* shape, int d, int K
 // Bound by HBM (every element read and written once).  VEC: d == 8 with
 // 16-byte aligned rows, 16-byte accesses with TR_ITEMS rows in flight per
 // thread: 36.6 -> 25 us for 32768 x 1024 float16 rows (rocprofv3, rows not
-// read before; 134 MB at 5.3 TB/s, what a large copy reaches; 40.8 -> 32.7 us
-// between HIP events in a training step).
+// read before; 134 MB at 5.3 TB/s, what a large copy reaches; 41 -> 30 us between
+// HIP events in a training step).
 constexpr int TR_ITEMS = 4;
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ X, int64_t ldx,
